@@ -120,7 +120,10 @@ typedef struct ltm_camera {
  * bit 4 (adjoint) merges consecutive samples of one trilinear cell in
  * registers before the LDS atomics; bit 5 (adjoint) instead keeps two planes
  * of corner sums across the ray's dominant axis, so a step along that axis
- * flushes 4 corners, not 8; bit 6 (with bit 3) makes the staggered starting
+ * flushes 4 corners, not 8 -- and, without bit 2, lets a camera whose rays run in
+ * narrow bundles (those of one lenslet and aperture sample, or of a small block
+ * of pixels, within about 2 voxels of each other) scatter whole bundles, which
+ * takes no part of the tiling but this flag; bit 6 (with bit 3) makes the staggered starting
  * offsets even, so rays that advance half a voxel per sample along that axis
  * cross its cell planes on the same iterations.  Each workgroup
  * marches its rays through consecutive slabs of chunk_mm camera depth,

@@ -13,10 +13,16 @@ namespace {
 
 uint64_t align256(uint64_t v) { return (v + 255u) & ~uint64_t(255u); }
 
+Accumulator plan_accumulators(const ltm_plan* p)
+{
+    return accumulators(p, reinterpret_cast<double*>(p->ws + p->accum_off), p->accum_words);
+}
+
 struct Dir {
     std::vector<uint32_t> items;   // (batch camera << kTileBits) | tile, by decreasing cost
     size_t lds = 0;                // dynamic LDS of the persistent kernel
     int blocks = 0;                // persistent workgroups
+    int kinds = 0;                 // bit 0: cameras scattered ray by ray, bit 1: in bundles
     uint64_t items_off = 0;
 };
 
@@ -74,11 +80,11 @@ ltm_status run_dir(ltm_batch* b, int d, hipStream_t s)
     hipError_t e = hipSuccess;
     if (d == LTM_ADJOINT)
         for (auto* p : b->plans) {
-            e = launch_fill64(reinterpret_cast<double*>(p->ws + p->accum_off), p->n_vox, s);
+            e = accumulator_clear(p, plan_accumulators(p), s);
             if (e != hipSuccess) return hip_fail(e, "batch zero accumulators");
         }
-    e = launch_batch(cams, items, (uint32_t)b->dir[d].items.size(), ctr, d, b->dir[d].blocks,
-                     b->dir[d].lds, s);
+    e = launch_batch(cams, items, (uint32_t)b->dir[d].items.size(), ctr, d, b->dir[d].kinds,
+                     b->dir[d].blocks, b->dir[d].lds, s);
     if (e != hipSuccess) return hip_fail(e, "batch sweep");
     if (d == LTM_ADJOINT)
         for (size_t k = 0; k < b->plans.size(); ++k) {
@@ -91,7 +97,7 @@ ltm_status run_dir(ltm_batch* b, int d, hipStream_t s)
                     break;
                 }
             if (!xout) continue;
-            e = launch_to_f32(reinterpret_cast<const double*>(p->ws + p->accum_off), xout, p->n_vox, s);
+            e = accumulator_convert(p, plan_accumulators(p), xout, s);
             if (e != hipSuccess) return hip_fail(e, "batch convert");
         }
     return LTM_OK;
@@ -135,8 +141,11 @@ ltm_status ltm_batch_create(ltm_plan* const* plans, uint32_t n_plans, ltm_batch*
                 delete b;
                 return fail(LTM_ERR_INVALID, "a camera has more than 2^20 tiles");
             }
-            order.push_back({(double)dv.items_per_split * dv.ru * dv.rv * dv.S, (uint32_t)q});
+            const double rays = dv.bundle ? (dv.ub_shared ? 1.0 : kThreads / 64) * dv.ub_u * dv.ub_v * dv.ub_r
+                                          : (double)dv.items_per_split * dv.ru * dv.rv;
+            order.push_back({rays * dv.S, (uint32_t)q});
             lds = std::max(lds, march_lds_bytes(dv, d));
+            b->dir[d].kinds |= dv.bundle ? 2 : 1;
         }
         std::stable_sort(order.begin(), order.end(),
                          [](const auto& a, const auto& c) { return a.first > c.first; });
@@ -204,10 +213,10 @@ ltm_status ltm_batch_bind(ltm_batch* b, void* ws, uint64_t bytes, const float* c
             bc.cam = bound_dev(p, p->cams[pc.second], d);
             bc.x = d == LTM_FORWARD ? x_in[pc.first] : x_out[pc.first];
             bc.y = y[pc.first];
-            bc.xacc = reinterpret_cast<double*>(p->ws + p->accum_off);
+            bc.xacc = accumulator_of(plan_accumulators(p), bc.cam);
             b->host_cams[d].push_back(bc);
         }
-        b->dir[d].blocks = cus * batch_blocks_per_cu(d, b->dir[d].lds);
+        b->dir[d].blocks = cus * batch_blocks_per_cu(d, b->dir[d].kinds, b->dir[d].lds);
         e = hipMemcpyAsync(b->ws + b->cams_off[d], b->host_cams[d].data(),
                            sizeof(BatchCam) * b->host_cams[d].size(), hipMemcpyHostToDevice, s);
         if (e == hipSuccess)

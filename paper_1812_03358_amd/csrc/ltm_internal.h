@@ -78,6 +78,15 @@ struct CamDev {
     int skew;             // adjoint: lanes start their sample walk at staggered offsets
     int merge;            // adjoint: merge consecutive samples of one cell in registers
     int window;           // adjoint: two planes of corner sums along the ray's dominant axis
+    // bundled adjoint: the grid axis nearest the optical axis and its sign
+    // along it; a unit of rays is ub_r aperture samples of ub_u x ub_v pixels,
+    // over nb_u x nb_v blocks (hexagonal cameras: blocks are lenslets, whose
+    // light falls around ub_cu, ub_cv pixels per lenslet coordinate from the
+    // detector's centre); ub_shared: a workgroup, not a wave, takes a unit;
+    // ub_rfast: consecutive units are aperture samples of one block
+    int bundle, dom, dom_sign, ub_u, ub_v, ub_r, ub_shared, ub_rfast, nb_u, nb_v, n_units;
+    float ub_cu, ub_cv;
+    int acc_zfast;        // adjoint: the accumulator is [y][x][z] (Accumulator::z), not [z][y][x]
     int groups_per_cu;    // 0, or the most workgroups one CU may hold (LDS reservation)
     int sub_n, sub_i;     // angular-sample subset: keep r with r mod sub_n == sub_i
     int items, items_per_split, tiles_u, tiles_v, n_tiles;
@@ -98,6 +107,16 @@ struct BatchCam {
     float* y;
     double* xacc;
 };
+// The adjoint's FP64 accumulators, N words each: [z][y][x], and [y][x][z] for
+// bundled cameras that look along z (their atomics walk 16 voxels of a column at a
+// time, contiguous there).  Either may be absent; the volume is their sum.
+struct Accumulator {
+    double* x = nullptr;
+    double* z = nullptr;
+};
+constexpr int kUnitRays = 128;    // rays a wave of the bundled adjoint holds at once
+constexpr int kSharedRays = 576;  // rays a workgroup of it holds at once (4 workgroups share a CU's LDS)
+constexpr int kPartRegs = 10;     // FP64 words per lane of a wave's partial sums (windows of up to 5 x 4)
 constexpr int kTileBits = 20;   // work item = (batch camera << 20) | tile
 
 struct CamHost {
@@ -123,7 +142,8 @@ struct ltm_plan {
     uint64_t n_vox = 0, n_meas = 0;
     uint64_t ws_bytes = 0;
     uint64_t counter_off = 0;   // 256-byte scratch word for ltm_plan_valid_rays
-    uint64_t accum_off = 0;     // N doubles: FP64 accumulator of the adjoint
+    uint64_t accum_off = 0;     // FP64 accumulators of the adjoint
+    uint64_t accum_words = 0;   // their doubles: N or 2 N
     uint32_t sub_n = 1, sub_i = 0;   // current angular-sample subset
     char* ws = nullptr;
     bool bound = false;
@@ -150,19 +170,30 @@ hipError_t launch_fill64(double* p, uint64_t n, hipStream_t s);
 // device address of the current GPU's fixed accumulator (kScratchVoxels doubles)
 hipError_t scratch_accumulator(double** out);
 hipError_t launch_to_f32(const double* a, float* b, uint64_t n, hipStream_t s);
+// the same from a [y][x][z] accumulator, plus (unless null) a [z][y][x] one
+hipError_t launch_zfast_to_f32(const double* az, const double* ax, float* b, const uint32_t n[3], hipStream_t s);
 // out[0] = sum (a - b)^2, out[1] = sum b^2 in FP64 (out: 2 doubles, cleared first)
 hipError_t launch_diff_sumsq(const float* a, const float* b, uint64_t n, double* out, hipStream_t s);
 hipError_t launch_fill(float* p, uint64_t n, float v, hipStream_t s);
 hipError_t launch_count(const CamDev& c, unsigned long long* counter, hipStream_t s);
 size_t march_lds_bytes(const CamDev& c, int dir);
 hipError_t launch_batch(const BatchCam* cams, const uint32_t* items, uint32_t n_items,
-                        unsigned int* counter, int dir, int blocks, size_t lds, hipStream_t s);
-int batch_blocks_per_cu(int dir, size_t lds);
+                        unsigned int* counter, int dir, int kinds, int blocks, size_t lds, hipStream_t s);
+int batch_blocks_per_cu(int dir, int kinds, size_t lds);
 
 // tiling limits (ltm_plan.cpp); sets the error message on failure
 ltm_status check_tiling(const ltm_grid& g, const ltm_camera& c, const ltm_tiling& t);
 
 // the camera's constants with the tables of one direction bound
 CamDev bound_dev(const ltm_plan* p, const CamHost& c, int dir);
+
+// Accumulators of the plan's adjoint in `words` words at base: both kinds if
+// its cameras call for both and they fit, else one for all.
+Accumulator accumulators(const ltm_plan* p, double* base, uint64_t words);
+// A camera's accumulator; sets d's layout to match.
+double* accumulator_of(const Accumulator& a, CamDev& d);
+// Clear the accumulators, and convert their sum to the FP32 volume.
+hipError_t accumulator_clear(const ltm_plan* p, const Accumulator& a, hipStream_t s);
+hipError_t accumulator_convert(const ltm_plan* p, const Accumulator& a, float* x, hipStream_t s);
 
 }  // namespace ltm

@@ -276,6 +276,11 @@ void camera_constants(const ltm_grid& g, const ltm_camera& c, CamDev& d)
         d.Et[a] = (float)(et[a] / g.pitch_mm);
         d.Ez[a] = (float)(ez[a] / g.pitch_mm);
     }
+    // the grid axis nearest the optical axis
+    d.dom = std::fabs(ez[2]) >= std::fabs(ez[0]) && std::fabs(ez[2]) >= std::fabs(ez[1])
+                ? 2
+                : (std::fabs(ez[1]) >= std::fabs(ez[0]) ? 1 : 0);
+    d.dom_sign = ez[d.dom] < 0.0 ? -1 : 1;
     d.zlo = (float)(-dA);
     d.invR = (float)(1.0 / ((double)c.rays_u * c.rays_v));
     d.inv_ru = (float)(1.0 / c.rays_u);
@@ -286,6 +291,117 @@ void camera_constants(const ltm_grid& g, const ltm_camera& c, CamDev& d)
     d.Ld = k_d.sL;
     d.Lg = k_g.sL;
     d.r2 = c.r_main_mm * c.r_main_mm;
+}
+
+// Units of the bundled adjoint (CamDev), or n_units = 0 where a unit's rays can
+// lie too far apart.  A wave sums a unit's samples in one cell layer into a
+// window of up to 5 x 4 voxels.  A window of W voxels holds any rays whose
+// spread across the layer plus their drift through it stays below W - 2 voxels;
+// a part of a unit that does not fit all the same is scattered in smaller parts.
+void bundle_geometry(const ltm_grid& g, const ltm_camera& c, CamDev& d)
+{
+    d.n_units = 0;
+    const double* es = c.axes;
+    const double* et = c.axes + 3;
+    const double* ez = c.axes + 6;
+    const double n[3] = {(double)g.nx, (double)g.ny, (double)g.nz};
+    // depth of the grid's centre, the grid's half extents along the camera's
+    // axes, and the largest slopes of rays from the lens to the grid
+    const double dA = -dot3(c.lens_center_mm, ez);
+    double ext_s = 0.0, ext_t = 0.0, depth = 0.0;
+    for (int k = 0; k < 3; ++k) {
+        ext_s += 0.5 * g.pitch_mm * n[k] * std::fabs(es[k]);
+        ext_t += 0.5 * g.pitch_mm * n[k] * std::fabs(et[k]);
+        depth += 0.5 * g.pitch_mm * n[k] * std::fabs(ez[k]);
+    }
+    ext_s += std::fabs(dot3(c.lens_center_mm, es)) + c.r_main_mm;
+    ext_t += std::fabs(dot3(c.lens_center_mm, et)) + c.r_main_mm;
+    if (!(dA > 1.01 * depth)) return;
+    const double us = ext_s / (dA - depth), vs = ext_t / (dA - depth);
+    const int t[2] = {d.dom == 0 ? 2 : 0, d.dom == 1 ? 2 : 1};
+    const double along = std::fabs(ez[d.dom]) - us * std::fabs(es[d.dom]) - vs * std::fabs(et[d.dom]);
+    if (!(along > 0.2)) return;
+    double drift[2];
+    for (int k = 0; k < 2; ++k)
+        drift[k] = (std::fabs(ez[t[k]]) + us * std::fabs(es[t[k]]) + vs * std::fabs(et[t[k]])) / along;
+    // spread in mm, anywhere in the grid, of rays whose detector positions
+    // differ by p pixels and whose aperture samples by h (of [-1, 1])
+    auto spread = [&](double p, double h) {
+        double w = 0.0;
+        for (double z : {-depth, depth})
+            w = std::max(w, std::fabs((double)d.Ad + z * d.Bd) * p + std::fabs((double)d.Ag + z * d.Bg) * h);
+        return w;
+    };
+    // instructions per sample step of the smallest window that holds rays
+    // spread by ws, wt mm, or 0 where none does
+    auto window = [&](double ws, double wt) {
+        double w[2];
+        for (int k = 0; k < 2; ++k)
+            w[k] = drift[k] + (ws * (std::fabs(es[t[k]]) + drift[k] * std::fabs(es[d.dom])) +
+                               wt * (std::fabs(et[t[k]]) + drift[k] * std::fabs(et[d.dom]))) / g.pitch_mm;
+        if (w[1] <= 0.95) return w[0] <= 0.95 ? 40.0 : (w[0] <= 1.95 ? 49.0 : (w[0] <= 2.95 ? 58.0 : 0.0));
+        if (w[1] > 1.95) return 0.0;
+        return w[0] <= 1.95 ? 62.0 : (w[0] <= 2.95 ? 73.0 : 0.0);
+    };
+    d.ub_shared = d.ub_rfast = 0;
+    const int R = (int)(c.rays_u * c.rays_v);
+    if (c.kind == LTM_SINGLE_LENS) {
+        // a block of pixels and part of an aperture row, or whole rows; the
+        // cost of a sample falls with the rays that share a window's set-up,
+        // folding and atomics (about 60 rays' worth of work)
+        static const int shapes[][2] = {{8, 8}, {4, 8}, {8, 4}, {4, 4}};
+        double best = 0.0;
+        for (const auto& sh : shapes)
+            for (int r = 1; r <= R; ++r) {
+                if (r < (int)c.rays_u ? c.rays_u % r != 0 : r % c.rays_u != 0) continue;
+                const int rays = sh[0] * sh[1] * r;
+                if (rays < 32 || rays > kSharedRays) continue;
+                const int across = std::min(r, (int)c.rays_u) - 1, rows = r / (int)c.rays_u - 1;
+                const double step = window(spread(sh[0] - 1, 2.0 * across / c.rays_u),
+                                           spread(sh[1] - 1, 2.0 * std::max(rows, 0) / c.rays_v));
+                const double cost = step * (1.0 + 60.0 / rays);
+                if (step == 0.0 || (best > 0.0 && cost >= best)) continue;
+                best = cost;
+                d.ub_u = sh[0];
+                d.ub_v = sh[1];
+                d.ub_r = r;
+                d.ub_shared = rays > kUnitRays;
+            }
+        if (best == 0.0) return;
+        d.nb_u = (int)((c.det_nu + d.ub_u - 1) / d.ub_u);
+        d.nb_v = (int)((c.det_nv + d.ub_v - 1) / d.ub_v);
+    } else {
+        // one aperture sample of one lenslet: the pixels whose rays pass the
+        // main lens lie within 2 r_main / |Ld| of each other
+        const bool hex = c.kind == LTM_PLENOPTIC_HEX;
+        const double reach = c.r_main_mm / std::fabs(d.Ld);
+        const double ku = hex ? 1e30 : (double)(c.det_nu / c.mla_nu), kv = hex ? 1e30 : (double)(c.det_nv / c.mla_nv);
+        if (!std::isfinite(reach) || window(spread(std::min(ku - 1.0, 2.0 * reach), 0.0),
+                                            spread(std::min(kv - 1.0, 2.0 * reach), 0.0)) == 0.0)
+            return;
+        d.ub_r = 1;
+        d.nb_u = (int)c.mla_nu;
+        d.nb_v = (int)c.mla_nv;
+        if (hex) {
+            double lg = 0.0;
+            for (double v : d.hLg) lg = std::max(lg, std::fabs(v));
+            const double half = std::ceil((c.r_main_mm + lg) / std::fabs(d.Ld)) + 2.0;
+            if (half > 128.0) return;
+            d.ub_u = d.ub_v = 2 * (int)half + 1;
+            d.ub_cu = (float)(-d.Lc / d.Ld);
+            d.ub_cv = (float)(-d.Lct / d.Ld);
+            // some 400 rays a unit, too few units for a wave each (the 2048^2
+            // camera at 20 degrees: 6.0 ms, half of it the last waves)
+            d.ub_shared = 1;
+        } else {
+            if (ku * kv > 65536.0) return;
+            d.ub_u = (int)ku;
+            d.ub_v = (int)kv;
+            d.ub_rfast = drift[0] < 0.3;
+        }
+    }
+    const uint64_t units = (uint64_t)d.nb_u * d.nb_v * ((R + d.ub_r - 1) / d.ub_r);
+    d.n_units = units < (1ull << 20) ? (int)units : 0;
 }
 
 // Tiling-dependent fields.
@@ -327,6 +443,23 @@ void apply_tiling(const ltm_grid& g, const ltm_camera& c, const ltm_tiling& t, C
     max_chunks = d.max_chunks;
 }
 
+// The camera's adjoint runs in bundles: its rays are narrow enough, and its
+// tiling asks for plane windows in FP64.
+bool runs_bundles(const CamHost& c)
+{
+    const uint32_t order = c.tiling[LTM_ADJOINT].order;
+    return c.dev.n_units > 0 && (order & 32) && !(order & 4);
+}
+
+// bit 0: some camera adds into a [z][y][x] accumulator, bit 1: some camera is
+// faster into a [y][x][z] one
+int accumulator_kinds(const ltm_plan* p)
+{
+    int kinds = 0;
+    for (const auto& c : p->cams) kinds |= runs_bundles(c) && c.dev.dom == 2 ? 2 : 1;
+    return kinds;
+}
+
 void layout(ltm_plan* p)
 {
     uint64_t off = 0;
@@ -344,7 +477,8 @@ void layout(ltm_plan* p)
     p->counter_off = off;
     off += 256;
     p->accum_off = off;
-    off = align256(off + sizeof(double) * p->n_vox);
+    p->accum_words = (accumulator_kinds(p) == 3 ? 2 : 1) * p->n_vox;
+    off = align256(off + sizeof(double) * p->accum_words);
     p->ws_bytes = off;
 }
 
@@ -405,11 +539,48 @@ ltm_status hip_fail(hipError_t e, const char* what)
 
 void clear_error() { g_err.clear(); }
 
+Accumulator accumulators(const ltm_plan* p, double* base, uint64_t words)
+{
+    const int kinds = accumulator_kinds(p);
+    // the [y][x][z] conversion's grid walks tiles of z in its second dimension
+    const bool z = (kinds & 2) && p->grid.nz <= 65535u * 32u;
+    Accumulator a;
+    if (kinds == 3 && z && words >= 2 * p->n_vox) {
+        a.x = base;
+        a.z = base + p->n_vox;
+    } else if (kinds == 2 && z) {
+        a.z = base;
+    } else {
+        a.x = base;
+    }
+    return a;
+}
+
+double* accumulator_of(const Accumulator& a, CamDev& d)
+{
+    d.acc_zfast = a.z && (!a.x || (d.bundle && d.dom == 2)) ? 1 : 0;
+    return d.acc_zfast ? a.z : a.x;
+}
+
+hipError_t accumulator_clear(const ltm_plan* p, const Accumulator& a, hipStream_t s)
+{
+    return launch_fill64(a.x ? a.x : a.z, (a.x && a.z ? 2 : 1) * p->n_vox, s);
+}
+
+hipError_t accumulator_convert(const ltm_plan* p, const Accumulator& a, float* x, hipStream_t s)
+{
+    if (!a.z) return launch_to_f32(a.x, x, p->n_vox, s);
+    const uint32_t n[3] = {p->grid.nx, p->grid.ny, p->grid.nz};
+    return launch_zfast_to_f32(a.z, a.x, x, n, s);
+}
+
 CamDev bound_dev(const ltm_plan* p, const CamHost& c, int dir)
 {
     CamDev d = c.dev;
     int nt, mc;
     apply_tiling(p->grid, c.desc, c.tiling[dir], d, nt, mc, c.chunk_floor[dir]);
+    d.bundle = dir == LTM_ADJOINT && runs_bundles(c);
+    if (d.bundle) d.n_tiles = d.ub_shared ? d.n_units : (d.n_units + kThreads / 64 - 1) / (kThreads / 64);
     if (dir == LTM_ADJOINT && !d.adj_f32) d.brick_cap /= 2;   // FP64 brick in the same LDS budget
     if (p->sub_n > 1) {
         // mean over the subset's samples: the view-subset operator (K/|S|) A_S
@@ -434,6 +605,24 @@ const char* last_error() { return g_err.c_str(); }
 }  // namespace ltm
 
 using namespace ltm;
+
+namespace {
+// x = A^T y through the given accumulators
+ltm_status adjoint(ltm_plan* p, const Accumulator& a, const float* y, float* x, hipStream_t s)
+{
+    hipError_t e = accumulator_clear(p, a, s);
+    if (e != hipSuccess) return hip_fail(e, "zero accumulator");
+    for (auto& c : p->cams) {
+        CamDev d = bound_dev(p, c, LTM_ADJOINT);
+        double* acc = accumulator_of(a, d);
+        e = launch_backproject(d, y, acc, s);
+        if (e != hipSuccess) return hip_fail(e, "backproject");
+    }
+    e = accumulator_convert(p, a, x, s);
+    if (e != hipSuccess) return hip_fail(e, "convert");
+    return LTM_OK;
+}
+}  // namespace
 
 extern "C" {
 
@@ -462,6 +651,7 @@ ltm_status ltm_plan_create(const ltm_grid* grid, const ltm_camera* cams, uint32_
             c.chunk_floor[dir] = c.tiling[dir].chunk_mm / 8.0;
         }
         camera_constants(*grid, cams[i], c.dev);
+        bundle_geometry(*grid, cams[i], c.dev);
         c.npix = (uint64_t)cams[i].det_nu * cams[i].det_nv;
         c.y_off = yoff;
         yoff += c.npix;
@@ -509,6 +699,7 @@ ltm_status ltm_plan_bind_workspace(ltm_plan* p, void* ws, uint64_t bytes, void* 
         for (int dir = 0; dir < 2; ++dir) {
             for (;;) {
                 const CamDev d = bound_dev(p, c, dir);
+                if (d.bundle) break;   // bundles use no tile or brick tables
                 hipError_t e = launch_setup(d, dir, s);
                 if (e != hipSuccess) return hip_fail(e, "tile setup");
                 if (!c.adapt[dir] || c.tiling[dir].chunk_mm * 0.5 < c.chunk_floor[dir] * 0.999) break;
@@ -607,17 +798,8 @@ ltm_status ltm_backproject(ltm_plan* p, const float* y, float* x, void* stream)
 {
     if (!p || !x || !y) return fail(LTM_ERR_INVALID, "null argument");
     if (!p->bound) return fail(LTM_ERR_WORKSPACE, "plan has no bound workspace");
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    double* acc = reinterpret_cast<double*>(p->ws + p->accum_off);
-    hipError_t e = launch_fill64(acc, p->n_vox, s);
-    if (e != hipSuccess) return hip_fail(e, "zero accumulator");
-    for (auto& c : p->cams) {
-        e = launch_backproject(bound_dev(p, c, LTM_ADJOINT), y, acc, s);
-        if (e != hipSuccess) return hip_fail(e, "backproject");
-    }
-    e = launch_to_f32(acc, x, p->n_vox, s);
-    if (e != hipSuccess) return hip_fail(e, "convert");
-    return LTM_OK;
+    return adjoint(p, accumulators(p, reinterpret_cast<double*>(p->ws + p->accum_off), p->accum_words), y, x,
+                   static_cast<hipStream_t>(stream));
 }
 
 ltm_status ltm_backproject_noalloc(ltm_plan* p, const float* y, float* x, void* stream)
@@ -628,19 +810,10 @@ ltm_status ltm_backproject_noalloc(ltm_plan* p, const float* y, float* x, void* 
                                          " voxels exceeds the fixed accumulator's " +
                                          std::to_string(kScratchVoxels));
     if (!p->bound) return fail(LTM_ERR_WORKSPACE, "plan has no bound workspace");
-    hipStream_t s = static_cast<hipStream_t>(stream);
     double* acc = nullptr;
-    hipError_t e = scratch_accumulator(&acc);
+    const hipError_t e = scratch_accumulator(&acc);
     if (e != hipSuccess) return hip_fail(e, "fixed accumulator address");
-    e = launch_fill64(acc, p->n_vox, s);
-    if (e != hipSuccess) return hip_fail(e, "zero accumulator");
-    for (auto& c : p->cams) {
-        e = launch_backproject(bound_dev(p, c, LTM_ADJOINT), y, acc, s);
-        if (e != hipSuccess) return hip_fail(e, "backproject");
-    }
-    e = launch_to_f32(acc, x, p->n_vox, s);
-    if (e != hipSuccess) return hip_fail(e, "convert");
-    return LTM_OK;
+    return adjoint(p, accumulators(p, acc, kScratchVoxels), y, x, static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"
