@@ -22,7 +22,7 @@ struct ltm_xport {
     ltm_grid grid;                 // the grid after the quarter turns (natural when q = 0)
     ltm_camera cam;
     uint32_t basis;
-    int kt;                        // angular rows (rays_v)
+    int kt = 0;                    // angular rows (plenoptic), or groups of them
     // host tables (FP32 values, built once)
     struct Band {
         int rows = 0, width = 0;
@@ -552,7 +552,6 @@ ltm_status ltm_xport_create(const ltm_grid* g, const ltm_camera* c, uint32_t bas
     t->grid = *g;
     t->cam = *c;
     t->basis = basis;
-    t->kt = (int)c->rays_v;
     t->rot = rot;
     t->nxr = nxr;
     t->nyr = (int)g->ny;
@@ -565,47 +564,67 @@ ltm_status ltm_xport_create(const ltm_grid* g, const ltm_camera* c, uint32_t bas
     const double r = c->r_main_mm, d0s = 2.0 * r / Ks, d0t = 2.0 * r / Kt;
     const double Vd = axis_volume((int)basis, D, dp, d0s) * axis_volume((int)basis, D, dp, d0t);
     const double scale = hz / ((double)Ks * Kt * Vd);
+    // Angular rows whose unmasked cells are the same columns have the same s
+    // factor, so their t factors add up and the group takes one pass of each
+    // kind: Sum_rows Bt X Cs^T = (Sum_rows Bt) X Cs^T.  An 8 x 8 grid has three
+    // groups (rows of 4, 6 and 8 cells inside the disc).
+    std::vector<std::vector<int>> groups, columns;
+    for (int kt = 0; kt < Kt; ++kt) {
+        const double tk = (kt + 0.5) * d0t - r;
+        std::vector<int> cells;
+        for (int ks = 0; ks < Ks; ++ks) {
+            const double sk = (ks + 0.5) * d0s - r;
+            if (sk * sk + tk * tk <= r * r) cells.push_back(ks);      // aperture mask
+        }
+        if (cells.empty()) continue;
+        size_t k = 0;
+        while (k < columns.size() && columns[k] != cells) ++k;
+        if (k == columns.size()) {
+            columns.push_back(cells);
+            groups.emplace_back();
+        }
+        groups[k].push_back(kt);
+    }
+    const int ng = (int)groups.size();
+    t->kt = ng;
     std::vector<Rows> bt_pairs, cs_pairs;
-    bt_pairs.reserve((size_t)nz * Kt);
-    cs_pairs.reserve((size_t)nz * Kt);
+    bt_pairs.reserve((size_t)nz * ng);
+    cs_pairs.reserve((size_t)nz * ng);
     std::vector<std::pair<int, double>> tmp;
     for (int iz = 0; iz < nz; ++iz) {
         const double z = L + (iz + 0.5 - 0.5 * nz) * hz;
-        for (int kt = 0; kt < Kt; ++kt) {
-            const double tk = (kt + 0.5) * d0t - r;
-            // t factor (shared by the row's cells; unit scale)
-            Rows bt(nv);
-            const Kernel1D kt1 = kernel_of((int)basis, z, D, F, tk, d0t, dp);
-            for (int v = 0; v < nv; ++v) factor_row(kt1, (v + 0.5 - 0.5 * nv) * dp, hy, ny, 1.0, bt[v]);
-            // s factors of the row's unmasked cells, summed, with the scale
-            std::vector<std::vector<double>> dense(nu);
-            std::vector<int> lo(nu, nx), hi(nu, -1);
-            for (int ks = 0; ks < Ks; ++ks) {
-                const double sk = (ks + 0.5) * d0s - r;
-                if (sk * sk + tk * tk > r * r) continue;              // aperture mask
-                const Kernel1D k1 = kernel_of((int)basis, z, D, F, sk, d0s, dp);
-                for (int u = 0; u < nu; ++u) {
+        // factors of the given cells of one axis, summed, per detector pixel
+        auto summed = [&](const std::vector<int>& cells, double d0, int n_det, double h, int n, double sc) {
+            std::vector<Kernel1D> kern;
+            for (int k : cells) kern.push_back(kernel_of((int)basis, z, D, F, (k + 0.5) * d0 - r, d0, dp));
+            Rows rows(n_det);
+            std::vector<double> dense(n, 0.0);
+            for (int i = 0; i < n_det; ++i) {
+                int lo = n, hi = -1;
+                for (const Kernel1D& k1 : kern) {
                     tmp.clear();
-                    factor_row(k1, (u + 0.5 - 0.5 * nu) * dp, hx, nx, scale, tmp);
-                    if (dense[u].empty() && !tmp.empty()) dense[u].assign(nx, 0.0);
+                    factor_row(k1, (i + 0.5 - 0.5 * n_det) * dp, h, n, sc, tmp);
                     for (const auto& kv : tmp) {
-                        dense[u][kv.first] += kv.second;
-                        lo[u] = std::min(lo[u], kv.first);
-                        hi[u] = std::max(hi[u], kv.first);
+                        dense[kv.first] += kv.second;
+                        lo = std::min(lo, kv.first);
+                        hi = std::max(hi, kv.first);
                     }
                 }
+                for (int j = lo; j <= hi; ++j) {
+                    if (dense[j] != 0.0) rows[i].emplace_back(j, dense[j]);
+                    dense[j] = 0.0;
+                }
             }
-            Rows cs(nu);
-            for (int u = 0; u < nu; ++u)
-                for (int j = lo[u]; j <= hi[u]; ++j)
-                    if (dense[u][j] != 0.0) cs[u].emplace_back(j, dense[u][j]);
-            bt_pairs.push_back(std::move(bt));
-            cs_pairs.push_back(std::move(cs));
+            return rows;
+        };
+        for (int k = 0; k < ng; ++k) {
+            bt_pairs.push_back(summed(groups[k], d0t, nv, hy, ny, 1.0));
+            cs_pairs.push_back(summed(columns[k], d0s, nu, hx, nx, scale));
         }
     }
     pack(bt_pairs, nv, t->bt);
     pack(cs_pairs, nu, t->cs);
-    const int pairs = nz * Kt;
+    const int pairs = nz * ng;
     transpose(t->cs, pairs, nx, t->cst);
     transpose(t->bt, pairs, ny, t->btt);
     if (rot) build_shears(t, g, sa, sb, hx, hz);
@@ -619,7 +638,7 @@ ltm_status ltm_xport_create(const ltm_grid* g, const ltm_camera* c, uint32_t bas
     place(t->off_cst_w, t->cst.w.size() * 4);
     place(t->off_btt_s, t->btt.start.size() * 4);
     place(t->off_btt_w, t->btt.w.size() * 4);
-    place(t->off_mid, mid * 4);
+    place(t->off_mid, mid * 4);   // the room of one row per group at most is used
     if (rot) place_shears(t, g, off);
     t->ws_bytes = off;
     add_turn(t, qm, gq);

@@ -19,7 +19,7 @@ struct BandDev {
 };
 
 struct XportDev {
-    int nx, ny, nz, nu, nv, kt;   // grid, detector, angular rows
+    int nx, ny, nz, nu, nv, kt;   // grid, detector, groups of angular rows with the same cells
     BandDev bt;    // t factor:      rows = detector rows,    columns = voxel rows (y)
     BandDev cs;    // s factor sum:  rows = detector columns, columns = voxel columns (x)
     BandDev cst;   // transpose of cs: rows = voxel columns,  columns = detector columns
