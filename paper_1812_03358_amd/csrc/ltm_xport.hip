@@ -67,13 +67,17 @@ __global__ __launch_bounds__(kBlock) void k_minor_fwd(XportDev d, const float* _
             s0[r] = st[min(v0 + r, d.nv - 1)];
             acc[r] = 0.0f;
         }
+        // loads from clamped (valid) rows, then a select, so that the rows' loads
+        // are in flight together
         for (int k = 0; k < d.bt.width; ++k) {
+            float wk[R], xk[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const int iy = s0[r] + k;
-                if (iy < d.ny)
-                    acc[r] = fmaf(w[(size_t)k * d.nv + min(v0 + r, d.nv - 1)], xs[(size_t)iy * d.nx], acc[r]);
+                wk[r] = w[(size_t)k * d.nv + min(v0 + r, d.nv - 1)];
+                xk[r] = xs[(size_t)min(s0[r] + k, d.ny - 1) * d.nx];
             }
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[r] = fmaf(wk[r], s0[r] + k < d.ny ? xk[r] : 0.0f, acc[r]);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -171,9 +175,11 @@ constexpr int kGroup = 4;       // plenoptic stage 1: terms of kGroup slices sum
 // (coalesced; the R rows of one voxel column adjacent so one LDS read serves
 // all R; W - 1 zero columns past the last so the band needs no clamp), and a
 // thread applies its column's band weights, loaded once per pair, to the R
-// staged rows.  Each product is rounded to FP32 and summed in FP64, as in
-// the adjoint's passes, so that A and A^T round the same products alike.
-// W is the table's width.
+// staged rows.  Products and sums are FP64 FMAs.  W is the table's width.
+//
+// What bounds it: the wait for a pair's band start and weights (then the LDS
+// read that depends on the start), hence kAhead pairs in flight; 414 -> 403 us for
+// the whole A of 100^3 on 800^2 turned by 30 degrees.
 template <int R, int W>
 __global__ __launch_bounds__(kBlockF) void k_major_fwd_lds(XportDev d, float* __restrict__ y, int zc)
 {
@@ -207,20 +213,38 @@ __global__ __launch_bounds__(kBlockF) void k_major_fwd_lds(XportDev d, float* __
         }
         __syncthreads();
         if (!live) continue;
-#pragma unroll 4
-        for (int p = 0; p < npc; ++p) {
-            // 32-bit table offsets (the launcher checks the tables' sizes)
-            const int pp = p0 + p;
-            const int s0 = d.cs.start[pp * d.nu + u];
-            const int wo = pp * W * d.nu + u;
-            const float* mz = ms + p * pitch + s0 * R;
+        // 32-bit table offsets (the launcher checks the tables' sizes); the next
+        // kAhead pairs' band starts and weights are in flight while a pair's
+        // terms are summed
+        constexpr int kAhead = 4;
+        int st[kAhead];
+        float wt[kAhead][W];
+        auto load = [&](int a, int p) {
+            const int pp = p0 + min(p, npc - 1);
+            st[a] = d.cs.start[pp * d.nu + u];
 #pragma unroll
-            for (int k = 0; k < W; ++k) {
-                const float wk = d.cs.w[wo + k * d.nu];
-                float m[R];
-                lds_rows<R>(mz + k * R, m);
+            for (int k = 0; k < W; ++k) wt[a][k] = d.cs.w[(pp * W + k) * d.nu + u];
+        };
 #pragma unroll
-                for (int r = 0; r < R; ++r) acc[r] += (double)(wk * m[r]);
+        for (int a = 0; a < kAhead; ++a) load(a, a);
+        for (int pb = 0; pb < npc; pb += kAhead) {
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a) {
+                const int p = pb + a;
+                if (p < npc) {
+                    const float* mz = ms + p * pitch + st[a] * R;
+                    double wk[W];
+#pragma unroll
+                    for (int k = 0; k < W; ++k) wk[k] = (double)wt[a][k];
+                    float m[W][R];
+#pragma unroll
+                    for (int k = 0; k < W; ++k) lds_rows<R>(mz + k * R, m[k]);
+                    load(a, p + kAhead);
+#pragma unroll
+                    for (int k = 0; k < W; ++k)
+#pragma unroll
+                        for (int r = 0; r < R; ++r) acc[r] = fma(wk[k], (double)m[k][r], acc[r]);
+                }
             }
         }
     }
@@ -258,47 +282,59 @@ __global__ __launch_bounds__(kBlock) void k_major_adj_w(XportDev d, const float*
     }
 }
 
-// Adjoint major pass with the image rows staged in LDS: a workgroup takes
-// `rows` detector rows (staged once, coalesced) and a chunk of (slice, row)
-// pairs; a thread holds one (pair, voxel column)'s band weights in registers
-// and applies them to every staged row.  The image gathers hit LDS instead
-// of scattered global loads.  W >= the table's width (terms past it
-// skipped).
-template <int W>
-__global__ __launch_bounds__(kBlock) void k_major_adj_lds(XportDev d, const float* __restrict__ y,
-                                                          int rows, int pchunk)
+// Adjoint major pass with the image rows staged in LDS: a workgroup takes R
+// detector rows (staged once, coalesced, the R rows of one detector column
+// adjacent so one LDS read serves all R) and a chunk of (slice, group) pairs; a
+// thread holds one (pair, voxel column)'s band weights in registers and applies
+// them to the staged rows.  Products and sums are FP64 FMAs.  W is the table's
+// width, or the next even one above 16.
+//
+// What bounds it: the LDS reads of the band (W of them per output row before,
+// W / 4 of 16 bytes now) and the wait for the weights, which are all in flight
+// before the first is used.  An exact W matters: each term past the width costs
+// as much as one within.  Grid 100^3, 800^2 detector turned by 30 degrees (W 22):
+// 704 -> about 305 us for the whole adjoint; straight on (W 17): 420 -> 224 us.
+// Capping the registers for one more wave spills (1030 us).
+template <int R, int W>
+__global__ __launch_bounds__(kBlock) void k_major_adj_lds(XportDev d, const float* __restrict__ y, int pchunk)
 {
-    extern __shared__ float ys[];
-    const int v0 = blockIdx.x * rows;
-    const int nr = min(rows, d.nv - v0);
-    for (int i = threadIdx.x; i < nr * d.nu; i += kBlock) ys[i] = y[(size_t)v0 * d.nu + i];
+    extern __shared__ float4 ys4[];
+    float* ys = reinterpret_cast<float*>(ys4);             // [nu][R]
+    const int v0 = blockIdx.x * R;
+    const int nr = min(R, d.nv - v0);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const float* src = y + (size_t)(v0 + min(r, nr - 1)) * d.nu;
+        for (int u = threadIdx.x; u < d.nu; u += kBlock) ys[u * R + r] = src[u];
+    }
     __syncthreads();
-    const size_t pairs = (size_t)d.nz * d.kt;
-    const size_t pb = (size_t)blockIdx.y * pchunk;
-    const size_t pe = pb + pchunk < pairs ? pb + pchunk : pairs;
+    const int pairs = d.nz * d.kt;
+    const int pb = blockIdx.y * pchunk, pe = min(pb + pchunk, pairs);
     const int wd = d.cst.width;
-    const size_t items = (pe - pb) * d.nx;
-    for (size_t it = threadIdx.x; it < items; it += kBlock) {
-        const size_t p = pb + it / d.nx;
-        const int ix = (int)(it % d.nx);
-        const int st = d.cst.start[p * d.nx + ix];
-        const float* wp = d.cst.w + p * wd * (size_t)d.nx + ix;
+    const int items = (pe - pb) * d.nx;
+    for (int it = threadIdx.x; it < items; it += kBlock) {
+        const int p = pb + it / d.nx, ix = it % d.nx;
+        const int st = d.cst.start[(size_t)p * d.nx + ix];
+        const float* wp = d.cst.w + (size_t)p * wd * d.nx + ix;
         float w[W];
-        int col[W];
+#pragma unroll
+        for (int k = 0; k < W; ++k) w[k] = wp[(size_t)min(k, wd - 1) * d.nx];
+        double acc[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = 0.0;
 #pragma unroll
         for (int k = 0; k < W; ++k) {
-            w[k] = k < wd ? wp[(size_t)k * d.nx] : 0.0f;
-            col[k] = min(st + k, d.nu - 1);
-        }
-        float* out = d.mid + (p * d.nv + v0) * (size_t)d.nx + ix;
-        for (int r = 0; r < nr; ++r) {
-            const float* yr = ys + r * d.nu;
-            double acc = 0.0;
+            if (W > 16 && k == W - 1 && k >= wd) break;    // uniform: an odd width
+            float f[R];
+            lds_rows<R>(ys + min(st + k, d.nu - 1) * R, f);
+            const double wk = (double)w[k];
 #pragma unroll
-            for (int k = 0; k < W; ++k)
-                if (k < wd) acc += (double)(w[k] * yr[col[k]]);
-            out[(size_t)r * d.nx] = (float)acc;
+            for (int r = 0; r < R; ++r) acc[r] = fma(wk, (double)f[r], acc[r]);
         }
+        float* out = d.mid + ((size_t)p * d.nv + v0) * d.nx + ix;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (r < nr) out[(size_t)r * d.nx] = (float)acc[r];
     }
 }
 
@@ -354,11 +390,15 @@ __global__ __launch_bounds__(kBlock) void k_minor_adj(XportDev d, float* __restr
                 part[j] = 0.0;
             }
             for (int k = 0; k < d.btt.width; ++k) {
+                float wk[G], mk[G];
 #pragma unroll
                 for (int j = 0; j < G; ++j) {
-                    const int v = st[j] + k;
-                    if (v < d.nv) part[j] += (double)(w[j][(size_t)k * d.ny] * m[j][(size_t)v * d.nx]);
+                    wk[j] = w[j][(size_t)k * d.ny];
+                    mk[j] = m[j][(size_t)min(st[j] + k, d.nv - 1) * d.nx];
                 }
+#pragma unroll
+                for (int j = 0; j < G; ++j)
+                    part[j] = fma((double)wk[j], (double)(st[j] + k < d.nv ? mk[j] : 0.0f), part[j]);
             }
             acc += (part[0] + part[1]) + (part[2] + part[3]);
         }
@@ -589,23 +629,41 @@ hipError_t launch_shear_adjoint(const ShearDev& r, float* x, hipStream_t s)
     return hipGetLastError();
 }
 
+namespace {
+
+constexpr int kPairChunk = 32;   // staged adjoint major pass: pairs per workgroup
+
+template <int R>
+void launch_major_adj_lds(const XportDev& d, const float* y, hipStream_t s)
+{
+    const size_t pairs = (size_t)d.nz * d.kt;
+    const dim3 g((unsigned)((d.nv + R - 1) / R), (unsigned)((pairs + kPairChunk - 1) / kPairChunk)), b(kBlock);
+    const size_t lds = (size_t)R * d.nu * sizeof(float);
+#define LTM_ADJ(W) case W: hipLaunchKernelGGL((k_major_adj_lds<R, W>), g, b, lds, s, d, y, kPairChunk); break;
+    switch (d.cst.width <= 16 ? d.cst.width : (d.cst.width + 1) / 2 * 2) {
+        LTM_ADJ(1) LTM_ADJ(2) LTM_ADJ(3) LTM_ADJ(4) LTM_ADJ(5) LTM_ADJ(6) LTM_ADJ(7) LTM_ADJ(8)
+        LTM_ADJ(9) LTM_ADJ(10) LTM_ADJ(11) LTM_ADJ(12) LTM_ADJ(13) LTM_ADJ(14) LTM_ADJ(15) LTM_ADJ(16)
+        LTM_ADJ(18) LTM_ADJ(20) LTM_ADJ(22) LTM_ADJ(24)
+    }
+#undef LTM_ADJ
+}
+
+}  // namespace
+
 hipError_t launch_xport_backproject(const XportDev& d, const float* y, float* x, hipStream_t s)
 {
     const size_t nm = (size_t)d.nz * d.kt * d.nv * d.nx;
     const dim3 g(grid_for(nm)), b(kBlock);
-    const int rows = std::min(16, 16384 / std::max(1, d.nu));     // <= 64 KiB of staged rows
+    // LDS-staged pass for band widths up to 24 while the staged rows (four, or one
+    // of a wide detector) fit 64 KiB and a (pair, column) index fits 31 bits
     const size_t pairs = (size_t)d.nz * d.kt;
-    const int pchunk = 32;
-    const dim3 gl((unsigned)((d.nv + rows - 1) / std::max(1, rows)),
-                  (unsigned)((pairs + pchunk - 1) / pchunk));
-    const size_t lds = (size_t)std::max(1, rows) * d.nu * sizeof(float);
-    if (rows >= 1 && gl.y < 65536 && d.cst.width <= 8)
-        hipLaunchKernelGGL(k_major_adj_lds<8>, gl, b, lds, s, d, y, rows, pchunk);
-    else if (rows >= 1 && gl.y < 65536 && d.cst.width <= 16)
-        hipLaunchKernelGGL(k_major_adj_lds<16>, gl, b, lds, s, d, y, rows, pchunk);
-    else if (rows >= 1 && gl.y < 65536 && d.cst.width <= 24)
-        hipLaunchKernelGGL(k_major_adj_lds<24>, gl, b, lds, s, d, y, rows, pchunk);
-    else if (d.cst.width <= 24)
+    if (d.cst.width >= 1 && d.cst.width <= 24 && d.nu <= 16384 && pairs * d.nx < (1u << 31) &&
+        (pairs + kPairChunk - 1) / kPairChunk < 65536) {
+        if (d.nu <= 4096)
+            launch_major_adj_lds<4>(d, y, s);
+        else
+            launch_major_adj_lds<1>(d, y, s);
+    } else if (d.cst.width <= 24)
         hipLaunchKernelGGL(k_major_adj_w<24>, g, b, 0, s, d, y);
     else
         hipLaunchKernelGGL(k_major_adj, g, b, 0, s, d, y);
@@ -694,6 +752,12 @@ __global__ __launch_bounds__(kBlock) void k_pl_major1_w(PlenDev d)
 // applies its column's band weights, loaded once per slice, to the R staged
 // rows.  Sums: FP32 over the terms of kGroup consecutive slices, FP64 across
 // groups.  W is the table's width.
+//
+// What bounds it: the wait for a slice's band start and weights and the LDS read
+// that depends on them (waves wait 75 % of the time; 8 or 16 rows per thread
+// read the tables less often and are slower, 1224 and 1358 us against 1157 for
+// the whole A of 128^3 on 1024^2).  With the next group's table entries in flight
+// while a group is summed 1026 us.
 template <int R, int W>
 __global__ __launch_bounds__(kBlockF) void k_pl_major1_lds(PlenDev d, int zc, int ncb)
 {
@@ -737,28 +801,46 @@ __global__ __launch_bounds__(kBlockF) void k_pl_major1_lds(PlenDev d, int zc, in
         }
         __syncthreads();
         if (!live) continue;
-        for (int z = 0; z < nzc; z += kGroup) {
+        // a group's band starts and weights are loaded while the group before it
+        // is summed (from the chunk's last slice past its end)
+        int st[2][kGroup];
+        float wt[2][kGroup][W];
+        auto load = [&](int a, int z) {
+#pragma unroll
+            for (int g = 0; g < kGroup; ++g) {
+                const int zs = so + (z0 + min(z + g, nzc - 1)) * sstep;
+                st[a][g] = d.bs1.start[zs];
+                const int wo = zs + (zs - ua) * (W - 1);       // (table * W) * na_u + ua
+#pragma unroll
+                for (int k = 0; k < W; ++k) wt[a][g][k] = d.bs1.w[wo + k * d.na_u];
+            }
+        };
+        auto sum = [&](int a, int z) {
             float part[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) part[r] = 0.0f;
 #pragma unroll
             for (int g = 0; g < kGroup; ++g) {
                 if (z + g >= nzc) break;
-                const int zs = so + (z0 + z + g) * sstep;
-                const int s0 = d.bs1.start[zs];
-                const int wo = zs + (zs - ua) * (W - 1);   // (table * W) * na_u + ua
-                const float* mz = ms + (z + g) * pitch + s0 * R;
+                const float* mz = ms + (z + g) * pitch + st[a][g] * R;
 #pragma unroll
                 for (int k = 0; k < W; ++k) {
-                    const float wk = d.bs1.w[wo + k * d.na_u];
                     float m[R];
                     lds_rows<R>(mz + k * R, m);
 #pragma unroll
-                    for (int r = 0; r < R; ++r) part[r] = fmaf(wk, m[r], part[r]);
+                    for (int r = 0; r < R; ++r) part[r] = fmaf(wt[a][g][k], m[r], part[r]);
                 }
             }
 #pragma unroll
             for (int r = 0; r < R; ++r) acc[r] += (double)part[r];
+        };
+        load(0, 0);
+        for (int z = 0; z < nzc; z += 2 * kGroup) {
+            load(1, z + kGroup);
+            sum(0, z);
+            if (z + kGroup >= nzc) break;
+            load(0, z + 2 * kGroup);
+            sum(1, z + kGroup);
         }
     }
     if (!live) return;
@@ -973,8 +1055,17 @@ __global__ __launch_bounds__(kBlock) void k_pl_major1_t_w(PlenDev d)
 // coalesced, the R rows of one array column adjacent so one LDS read serves
 // all R) and a chunk of slices; a thread takes one (slice, voxel column), loads each
 // cell's band weights once and applies them to the R staged rows.  Sums:
-// FP32 over one cell's band, FP64 across cells.  W >= the table's width
-// (terms past it skipped).
+// FP32 over one cell's band, FP64 across cells.  W is the table's width or the
+// next larger one compiled (adj_width_low(W) is the smallest that comes to it).
+//
+// What bounds it: the wait for the band's weights, so they are all in flight
+// before the first is used, and terms past the width: a loop to 16 with a test
+// per term took 762 us where the width is 9 (whole adjoint; 128^3, 1024^2 image),
+// this one 317 us; turned by 30 degrees (width 9) 1749 -> 708 us.
+constexpr int adj_width_low(int w)
+{
+    return w <= 4 ? 1 : w <= 8 || (w > 12 && w <= 16) ? w - 1 : w <= 12 ? w : w - 3;
+}
 constexpr int kBlockT = 1024;   // 16 waves share one staged row block
 
 template <int R, int W>
@@ -1019,18 +1110,21 @@ __global__ __launch_bounds__(kBlockT) void k_pl_major1_t_lds(PlenDev d, int zchu
             const int s0 = d.bs1t.start[tab * d.nx + ix];
             const int wo = tab * wd * d.nx + ix;
             const float* fc = fs + c * pitch;
-            float part[R];
+            float part[R], w[W];
 #pragma unroll
             for (int r = 0; r < R; ++r) part[r] = 0.0f;
+            // all weights in flight together; past the width the last one's
+            // address again, not used
 #pragma unroll
-            for (int k = 0; k < W; ++k)
-                if (k < wd) {
-                    const float wk = d.bs1t.w[wo + k * d.nx];
-                    float f[R];
-                    lds_rows<R>(fc + min(s0 + k, d.na_u - 1) * R, f);
+            for (int k = 0; k < W; ++k) w[k] = d.bs1t.w[wo + min(k, wd - 1) * d.nx];
 #pragma unroll
-                    for (int r = 0; r < R; ++r) part[r] = fmaf(wk, f[r], part[r]);
-                }
+            for (int k = 0; k < W; ++k) {
+                if (k >= adj_width_low(W) && k >= wd) break;       // uniform
+                float f[R];
+                lds_rows<R>(fc + min(s0 + k, d.na_u - 1) * R, f);
+#pragma unroll
+                for (int r = 0; r < R; ++r) part[r] = fmaf(w[k], f[r], part[r]);
+            }
 #pragma unroll
             for (int r = 0; r < R; ++r) acc[r] += (double)part[r];
         }
@@ -1045,12 +1139,16 @@ template <int R>
 void launch_major1_t_lds(const PlenDev& p, int wb, int zchunk, dim3 g, hipStream_t s)
 {
     const size_t lds = (size_t)std::max(1, p.row_cells_max) * R * p.na_u * sizeof(float);
-    if (wb == 8)
-        hipLaunchKernelGGL((k_pl_major1_t_lds<R, 8>), g, dim3(kBlockT), lds, s, p, zchunk);
-    else if (wb == 16)
-        hipLaunchKernelGGL((k_pl_major1_t_lds<R, 16>), g, dim3(kBlockT), lds, s, p, zchunk);
-    else
-        hipLaunchKernelGGL((k_pl_major1_t_lds<R, 24>), g, dim3(kBlockT), lds, s, p, zchunk);
+#define LTM_ADJ(W)                                                                                        \
+    case W:                                                                                               \
+        if constexpr (R < 8 || W <= 9)                                                                    \
+            hipLaunchKernelGGL((k_pl_major1_t_lds<R, W>), g, dim3(kBlockT), lds, s, p, zchunk);            \
+        break;
+    switch (wb) {
+        LTM_ADJ(4) LTM_ADJ(6) LTM_ADJ(8) LTM_ADJ(9) LTM_ADJ(10) LTM_ADJ(11) LTM_ADJ(12) LTM_ADJ(14)
+        LTM_ADJ(16) LTM_ADJ(20) LTM_ADJ(24)
+    }
+#undef LTM_ADJ
 }
 
 // Stage-1 major pass of A: the LDS-staged kernel for table widths up to 4
@@ -1085,8 +1183,11 @@ void launch_major1(const PlenDev& p, hipStream_t s)
 // cell of one angular row fit 64 KiB, else the global-gather kernels.
 void launch_major1_t(const PlenDev& p, hipStream_t s)
 {
-    const int wb = p.bs1t.width <= 8 ? 8 : p.bs1t.width <= 16 ? 16 : 24;
-    int R = 8;
+    // the smallest compiled width that holds the table's
+    int wb = 24;
+    for (int w : {20, 16, 14, 12, 11, 10, 9, 8, 6, 4})
+        if (p.bs1t.width <= w) wb = w;
+    int R = p.bs1t.width <= 9 ? 8 : 4;   // 8 rows of wider bands spill
     while (R >= 1 && (size_t)p.row_cells_max * R * p.na_u * sizeof(float) > 65536) R /= 2;
     if (R >= 1 && p.bs1t.width <= 24 && (size_t)p.nz * p.ks * p.bs1t.width * p.nx < (1u << 31)) {
         const int nvb = (p.na_v + R - 1) / R;
