@@ -33,6 +33,30 @@ __device__ __forceinline__ u16 f2bf(float f)
     return (u16)(u >> 16);
 }
 
+// Where the 8-channel group g of voxel v of a staged halo lies: at v * (CIN / 8) +
+// (g ^ conv_swizzle<CIN>(v)), in units of 16 bytes.  One clock of a 16-byte read
+// serves lanes 0..3 and 20..23 (and so on): four voxels' group g and the next
+// four's group g + 1.  They fall on different banks as they are for 32-byte
+// voxels, and with this exchange of groups for 64-byte ones and multiples.
+template <int CIN>
+__device__ __forceinline__ int conv_swizzle(int v)
+{
+    return CIN % 64 == 0 ? (v & 3) << 1 : CIN % 32 == 0 ? v & 2 : 0;
+}
+
+// Kernels that end in a global atomic per workgroup on the same few addresses: one
+// workgroup of 16 waves per compute unit, as the atomics of one address take
+// about 12 (maxima) to 28 ns (sums) each, one after the other.  With 1024
+// workgroups of 4 waves the maximum of 128^3 values took 51 us, the masked
+// gradient with its bias sums 29 us however small; now 3 and 15 us.
+constexpr unsigned kSumBlock = 1024;
+
+unsigned sum_blocks(size_t n)
+{
+    const size_t b = (n + kSumBlock - 1) / kSumBlock;
+    return (unsigned)(b > 256 ? 256 : (b ? b : 1));
+}
+
 union Frag {
     bf16x8 v;
     uint4 q;
@@ -179,51 +203,283 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvFwd a)
         }
 }
 
-// 3x3x3 convolution with at most 64 input channels, its input tile staged
-// in LDS: a workgroup computes a 16 x 4 x TZ (x, y, z) block of output voxels
-// (wave w: row y0 + w, its TZ tiles the TZ z planes, 16 voxels along x each)
-// and stages the block's input halo (18 x 6 x (TZ + 2) voxels, all channels,
-// zero outside the grid; the upsampled and the concatenated inputs resolved
-// while staging) once, so each A fragment is one 16-byte LDS read instead of
-// a global gather.  K runs over (tap, channel) as in the packed weights.
+// The block of a 3-D grid that this workgroup takes.  Workgroups go to the
+// eight XCDs in turn, each with an L2 of its own: each XCD takes one contiguous
+// range of the blocks, so that neighbours read their common halo through one L2.
+__device__ __forceinline__ int3 xcd_block()
+{
+    const unsigned id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    const unsigned n = gridDim.x * gridDim.y * gridDim.z, x = id & 7;
+    const unsigned b = x * (n >> 3) + min(x, n & 7) + (id >> 3);
+    const unsigned r = b / gridDim.x;
+    return int3{(int)(b - r * gridDim.x), (int)(r % gridDim.y), (int)(r / gridDim.y)};
+}
+
 constexpr int kTX = 16, kTY = 4;
 constexpr int kHX = kTX + 2, kHY = kTY + 2;
 
+// What a tap outside the grid reads: selecting the address rather than the loaded
+// value keeps a thread's loads in flight together.
+__device__ __attribute__((aligned(16))) unsigned kZeroVoxel[4];
+
+__device__ __forceinline__ uint4 load_or_zero(const u16* p, bool ok)
+{
+    // both addresses in the global address space: a generic load would also wait
+    // for LDS
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(1))) u32x4* GlobalPtr;
+    const u32x4 q = *(ok ? (GlobalPtr)p : (GlobalPtr)kZeroVoxel);
+    return uint4{q.x, q.y, q.z, q.w};
+}
+
+// The 8 channels [ci, ci + 8) of input voxel (x, y, z) on the output grid (the
+// upsampled and the concatenated inputs resolved), zero outside the grid.
+__device__ __forceinline__ uint4 conv_input(const ConvFwd& a, int x, int y, int z, int ci)
+{
+    const bool ok = (unsigned)x < (unsigned)a.W && (unsigned)y < (unsigned)a.H && (unsigned)z < (unsigned)a.D;
+    const int xc = ok ? x : 0, yc = ok ? y : 0, zc = ok ? z : 0;
+    const u16* src = ci < a.c0
+        ? a.in0 + (((size_t)(zc >> a.up) * (a.H >> a.up) + (yc >> a.up)) * (a.W >> a.up) + (xc >> a.up)) * a.c0 + ci
+        : a.in1 + (((size_t)zc * a.H + yc) * a.W + xc) * a.c1 + (ci - a.c0);
+    return load_or_zero(src, ok);
+}
+
+// Whether four channels of an output voxel can be stored at once.
+__device__ __forceinline__ bool conv_vec(const ConvFwd& a)
+{
+    return ((a.split | (a.cout - a.split)) & 3) == 0 &&
+           ((reinterpret_cast<uintptr_t>(a.out) | reinterpret_cast<uintptr_t>(a.out2)) & 15) == 0;
+}
+
+// Two floats rounded to nearest even BF16 (NaN stays NaN).
+__device__ __forceinline__ unsigned f2bf2(float lo, float hi)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 v{(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(unsigned, v);
+}
+
+// Bias, ReLU and store (BF16 or FP32, split in two channel ranges for the input
+// gradient of a concatenation) of a wave's M x NW accumulators: vox(m) is the lane's
+// voxel of row m (negative: none), [c16 + 16 t + 4 kg, + 4) its channels.
+template <int M, int NW, class Vox>
+__device__ __forceinline__ void conv_epilogue(const ConvFwd& a, const f32x4 (&acc)[M][NW], int c16, int kg, Vox vox)
+{
+    const bool vec = conv_vec(a);
+#pragma unroll
+    for (int t = 0; t < NW; ++t) {
+        const int co = c16 + t * 16 + 4 * kg;
+        if (co >= a.cout) continue;
+        float b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = a.bias && co + i < a.cout ? a.bias[co + i] : 0.0f;
+        auto value = [&](int m, int i) {
+            const float v = acc[m][t][i] + b[i];
+            return a.relu ? fmaxf(v, 0.0f) : v;
+        };
+        if (vec) {
+            const bool first = co < a.split;
+            const int st = first ? a.split : a.cout - a.split, c = first ? co : co - a.split;
+            void* out = first ? a.out : a.out2;
+            if (a.out_f32) {
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const int v = vox(m);
+                    if (v >= 0)
+                        *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + (size_t)(unsigned)v * (unsigned)st + c) =
+                            float4{value(m, 0), value(m, 1), value(m, 2), value(m, 3)};
+                }
+            } else {
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const int v = vox(m);
+                    if (v >= 0)
+                        *reinterpret_cast<uint2*>(reinterpret_cast<u16*>(out) + (size_t)(unsigned)v * (unsigned)st + c) =
+                            uint2{f2bf2(value(m, 0), value(m, 1)), f2bf2(value(m, 2), value(m, 3))};
+                }
+            }
+            continue;
+        }
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const int v = vox(m);
+            if (v < 0) continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (co + i >= a.cout) continue;
+                const bool first = co + i < a.split;
+                const size_t o = first ? (size_t)v * a.split + co + i
+                                       : (size_t)v * (a.cout - a.split) + (co + i - a.split);
+                void* out = first ? a.out : a.out2;
+                if (a.out_f32) reinterpret_cast<float*>(out)[o] = value(m, i);
+                else reinterpret_cast<u16*>(out)[o] = (u16)f2bf2(value(m, i), 0.0f);
+            }
+        }
+    }
+}
+
+// 3x3x3 convolution of CIN = 16, 32 or 64 input channels, its input tile staged in
+// LDS: a workgroup computes a 16 x 4 x TZ (x, y, z) block of output voxels and
+// stages the block's input halo (18 x 6 x (TZ + 2) voxels, all channels) once,
+// so each voxel fragment is one 16-byte LDS read instead of a global gather.  K
+// runs over (tap, channel) as in the packed weights.  WN waves share a row of
+// voxels and split the output channels, so a wave has WN rows x TZ planes of 16
+// voxels and NT / WN channel tiles.  The weights are the matrix instruction's
+// first operand: a lane then holds four consecutive channels of one voxel and
+// stores them at once.
+//
+// What bounds it: the issue of vector instructions around the matrix ones, and the
+// wait for the halo.  So a thread stages one (x, channel group) of many rows, all
+// their loads in flight; the steps are unrolled, their LDS offsets immediates from
+// a few lane bases; the weights' addresses are scalar.  WN is what reads the
+// weights seldom enough: 64 -> 32 channels at 64^3, WN 1 112 us, WN 2 70 us.  Of
+// the kernel with one staging load in flight, scattered stores and table offsets
+// to this one: 16 -> 16 channels at 128^3 82 -> 61 us, 32 -> 16 163 -> 104, 64 -> 32
+// at 64^3 137 -> 70 (418 TFLOP/s), 32 -> 32 at 64^3 46 -> 24 us.
+template <int CIN, int NT, int TZ, int WN>
+__global__ __launch_bounds__(256) void k_conv_fwd_tile(ConvFwd a)
+{
+    constexpr int kHZ = TZ + 2, NW = NT / WN, G = CIN / 8, kSteps = (27 * CIN + 31) / 32;
+    extern __shared__ uint4 hs4[];                         // [kHZ][kHY][kHX][G], swizzled
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, kg = lane >> 4;
+    const int3 blk = xcd_block();
+    const int x0 = blk.x * kTX, y0 = blk.y * kTY, z0 = blk.z * TZ;
+    {
+        constexpr int kRow = kHX * G, kRows = kHY * kHZ;   // 16-byte items of a halo row, rows
+        constexpr int kPass = 256 / kRow, kTrips = (kRows + kPass - 1) / kPass;
+        constexpr int kBatch = kTrips <= 12 ? kTrips : (kTrips + 1) / 2;
+        const int row0 = threadIdx.x / kRow, it = threadIdx.x % kRow, hx = it / G, g = it % G;
+        const bool first = g * 8 < a.c0;
+        const int sh = first ? a.up : 0, cst = first ? a.c0 : a.c1;
+        const u16* src = first ? a.in0 + g * 8 : a.in1 + (g * 8 - a.c0);
+        const int x = x0 + hx - 1, Wl = a.W >> sh, Hl = a.H >> sh;
+        const bool okx = (unsigned)x < (unsigned)a.W;
+        if (row0 < kPass)
+#pragma unroll
+            for (int b0 = 0; b0 < kTrips; b0 += kBatch) {
+                uint4 q[kBatch];
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    const int row = row0 + (b0 + j) * kPass, hz = row / kHY, hy = row - hz * kHY;
+                    const int y = y0 + hy - 1, z = z0 + hz - 1;
+                    const bool ok = okx && (unsigned)y < (unsigned)a.H && (unsigned)z < (unsigned)a.D;
+                    const int vox = ok ? ((z >> sh) * Hl + (y >> sh)) * Wl + (x >> sh) : 0;
+                    q[j] = load_or_zero(src + (size_t)(unsigned)vox * (unsigned)cst, ok);
+                }
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    const int row = row0 + (b0 + j) * kPass, vox = row * kHX + hx;
+                    if (row < kRows) hs4[vox * G + (g ^ conv_swizzle<CIN>(vox))] = q[j];
+                }
+            }
+    }
+    const int wy = wave / WN * WN, c16 = wave % WN * NW * 16;
+    // the fragment at tap (dz, dy, dx) of the lane's voxel (x0 + r, y0 + wy + j,
+    // z0 + m) starts at halo voxel vb + c, c = (m + dz) 108 + (j + dy) 18 + dx (taps
+    // counted from 0); the swizzle repeats with c mod 4
+    const int vb = wy * kHX + r;
+    constexpr int kBases = CIN == 16 ? 4 : 4 * (CIN / 32);
+    int base[kBases];
+    if constexpr (CIN == 16) {
+        // a step's taps t and t + 1 are 1, 16 (next row) or 70 (next plane) voxels
+        // apart; the last step has tap 26 alone
+        base[0] = (vb + (kg >> 1)) * G + (kg & 1);
+        base[1] = (vb + (kg >> 1) * 16) * G + (kg & 1);
+        base[2] = (vb + (kg >> 1) * 70) * G + (kg & 1);
+        base[3] = vb * G + (kg & 1);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kBases; ++i)
+            base[i] = vb * G + ((kg + i / 4 * 4) ^ conv_swizzle<CIN>(vb + i % 4));
+    }
+    f32x4 acc[WN * TZ][NW];
+#pragma unroll
+    for (int m = 0; m < WN * TZ; ++m)
+#pragma unroll
+        for (int t = 0; t < NW; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the weight fragments of the next P steps are in flight
+    constexpr int P = NW == 1 ? 6 : NW == 2 ? (TZ == 8 ? 3 : 4) : 2;
+    const unsigned boff = (unsigned)(r * a.Kp + 8 * kg);
+    Frag Bq[P][NW];
+    auto loadB = [&](Frag (&b)[NW], int ks) {
+#pragma unroll
+        for (int t = 0; t < NW; ++t)
+            b[t].q = *reinterpret_cast<const uint4*>(a.wt + (size_t)(c16 + t * 16) * a.Kp + ks * 32 + boff);
+    };
+#pragma unroll
+    for (int p = 0; p < P; ++p) loadB(Bq[p], p);
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+        const int tap = s * 32 / CIN;
+        const int tv = (tap / 9 * kHY + tap / 3 % 3) * kHX + tap % 3;
+        const bool pad = CIN == 16 && s == kSteps - 1;
+        Frag A[WN * TZ];
+#pragma unroll
+        for (int m = 0; m < WN * TZ; ++m) {
+            const int c = tv + m / WN * (kHY * kHX) + m % WN * kHX;
+            const int bi = CIN == 16 ? (pad ? 3 : tap % 3 != 2 ? 0 : tap % 9 != 8 ? 1 : 2)
+                                     : c % 4 + s % (CIN / 32 + (CIN == 16)) * 4;
+            A[m].q = hs4[base[bi] + c * G];
+            if (pad && kg >= 2) A[m].q = uint4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int m = 0; m < WN * TZ; ++m)
+#pragma unroll
+            for (int t = 0; t < NW; ++t)
+                acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Bq[s % P][t].v, A[m].v, acc[m][t], 0, 0, 0);
+        if (s + P < kSteps) loadB(Bq[s % P], s + P);
+    }
+    // epilogue: rows 4 kg .. 4 kg + 3 of column r are four channels of voxel x0 + r
+    conv_epilogue(a, acc, c16, kg, [&](int m) {
+        const int z = z0 + m / WN, y = y0 + wy + m % WN;
+        return x0 + r < a.W && y < a.H && z < a.D ? (z * a.H + y) * a.W + x0 + r : -1;
+    });
+}
+
+// The same for any other multiple of 8 input channels up to 64: halo offsets from
+// a table in LDS, a wave has one row of voxels and all channel tiles.
 template <int NT, int TZ>
 __global__ __launch_bounds__(256) void k_conv_fwd_lds(ConvFwd a)
 {
-    constexpr int kTZ = TZ, kHZ = TZ + 2;
+    constexpr int kHZ = TZ + 2, NW = NT, M = TZ;
     extern __shared__ uint4 hs4[];
     u16* hs = reinterpret_cast<u16*>(hs4);                 // [kHZ][kHY][kHX][cin]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, kg = lane >> 4;
     const int cin = a.c0 + a.c1;
-    const int Din = a.D >> a.up, Hin = a.H >> a.up, Win = a.W >> a.up;
-    const int x0 = blockIdx.x * kTX, y0 = blockIdx.y * kTY, z0 = blockIdx.z * kTZ;
-    // stage the halo in 8-channel groups (16 bytes; c0 and c1 are multiples of 8)
+    const int3 blk = xcd_block();
+    const int x0 = blk.x * kTX, y0 = blk.y * kTY, z0 = blk.z * TZ;
+    // stage the halo in 8-channel groups (16 bytes; c0 and c1 are multiples of 8),
+    // kStage of them in flight per thread: one trip at the most channels that this
+    // TZ is chosen for
+    constexpr int kStage = TZ == 8 ? 9 : TZ == 4 ? 11 : 14;
     const int groups = cin >> 3;
     // groups is a power of two for 8, 16, 32 and 64 channels: split i by shifts
     const bool gpow2 = (groups & (groups - 1)) == 0;
     const int lg = __ffs(groups) - 1;
-    for (int i = threadIdx.x; i < kHX * kHY * kHZ * groups; i += 256) {
-        const int g = gpow2 ? (i & (groups - 1)) : i % groups;
-        const int vox = gpow2 ? (i >> lg) : i / groups;
-        const int hx = vox % kHX, hy = (vox / kHX) % kHY, hz = vox / (kHX * kHY);
-        const int x = x0 + hx - 1, y = y0 + hy - 1, z = z0 + hz - 1;
-        const bool ok = (unsigned)x < (unsigned)a.W && (unsigned)y < (unsigned)a.H && (unsigned)z < (unsigned)a.D;
-        const int xc = ok ? x : 0, yc = ok ? y : 0, zc = ok ? z : 0;
-        const int ci = g * 8;
-        const u16* src = ci < a.c0
-            ? a.in0 + (((size_t)(zc >> a.up) * Hin + (yc >> a.up)) * Win + (xc >> a.up)) * a.c0 + ci
-            : a.in1 + (((size_t)zc * a.H + yc) * a.W + xc) * a.c1 + (ci - a.c0);
-        const uint4 q = *reinterpret_cast<const uint4*>(src);
-        *reinterpret_cast<uint4*>(hs + (size_t)vox * cin + ci) = ok ? q : uint4{0u, 0u, 0u, 0u};
+    const int items = kHX * kHY * kHZ * groups;
+    for (int i0 = threadIdx.x; i0 < items; i0 += 256 * kStage) {
+        uint4 q[kStage];
+        int dst[kStage];
+#pragma unroll
+        for (int j = 0; j < kStage; ++j) {
+            const int i = min(i0 + 256 * j, items - 1);
+            const int g = gpow2 ? (i & (groups - 1)) : i % groups;
+            const int vox = gpow2 ? (i >> lg) : i / groups;
+            const int hx = vox % kHX, hy = (vox / kHX) % kHY, hz = vox / (kHX * kHY);
+            dst[j] = vox * cin + g * 8;
+            q[j] = conv_input(a, x0 + hx - 1, y0 + hy - 1, z0 + hz - 1, g * 8);
+        }
+        // an index past the last repeats the last: the same value again
+#pragma unroll
+        for (int j = 0; j < kStage; ++j) *reinterpret_cast<uint4*>(hs + dst[j]) = q[j];
     }
-    (void)Din;
     // per K-step and lane group: the halo offset (in u16) of the 8 channels
     // [ci, ci + 8) of tap (dz, dy, dx), relative to the lane's output voxel;
     // steps past the 27 taps (K padding, zero weights) point at offset 0 and
-    // their A fragment is zeroed below
+    // their voxel fragment is zeroed below
     const int nsteps = a.Kp >> 5;
     int* koff = reinterpret_cast<int*>(hs + (size_t)kHX * kHY * kHZ * cin);
     for (int i = threadIdx.x; i < nsteps * 4; i += 256) {
@@ -237,203 +493,240 @@ __global__ __launch_bounds__(256) void k_conv_fwd_lds(ConvFwd a)
         koff[i] = off;
     }
     __syncthreads();
-    f32x4 acc[kTZ][NT];
+    f32x4 acc[M][NW];
 #pragma unroll
-    for (int m = 0; m < kTZ; ++m)
+    for (int m = 0; m < M; ++m)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < NW; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     // the lane's output voxel (x0 + r, y0 + wave, z0 + m) sits at halo
     // (1 + r, 1 + wave, 1 + m)
     const u16* abase = hs + (size_t)(((1 * kHY + 1 + wave) * kHX) + 1 + r) * cin;
-    const size_t mstride = (size_t)kHY * kHX * cin;
+    const int zstride = kHY * kHX * cin;
     const u16* bbase = a.wt + (size_t)r * a.Kp + 8 * kg;
-    if constexpr (NT == 1) {
-        // two steps per trip with alternating operand buffers: the B fragments
-        // and the offset of the next step are loaded while a step runs its MFMAs;
-        // only the last step can hold K padding, so it alone (peeled) selects
-        auto loadB = [&](Frag (&b)[NT], int ks) {
+    auto loadB = [&](Frag (&b)[NW], int ks) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
-                b[t].q = *reinterpret_cast<const uint4*>(bbase + (size_t)t * 16 * a.Kp + ks * 32);
-        };
-        auto mma = [&](const Frag (&b)[NT], int off, bool pad_step, int ks) {
-            const bool ok = !pad_step || (ks * 32 + 8 * kg) < 27 * cin;
-            Frag A[kTZ];
+        for (int t = 0; t < NW; ++t)
+            b[t].q = *reinterpret_cast<const uint4*>(bbase + (size_t)t * 16 * a.Kp + ks * 32);
+    };
+    // only the last step can hold K padding
+    auto mma = [&](const Frag (&b)[NW], int off, bool pad_step, int ks) {
+        const bool ok = !pad_step || (ks * 32 + 8 * kg) < 27 * cin;
+        Frag A[M];
 #pragma unroll
-            for (int m = 0; m < kTZ; ++m) {
-                A[m].q = *reinterpret_cast<const uint4*>(abase + m * mstride + off);
-                if (pad_step) A[m].q = ok ? A[m].q : uint4{0u, 0u, 0u, 0u};
-            }
-#pragma unroll
-            for (int m = 0; m < kTZ; ++m)
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[m].v, b[t].v, acc[m][t], 0, 0, 0);
-        };
-        Frag B0[NT], B1[NT];
-        int off0 = koff[kg], off1 = 0;
-        loadB(B0, 0);
-        int ks = 0;
-        for (; ks + 2 < nsteps; ks += 2) {
-            loadB(B1, ks + 1);
-            off1 = koff[(ks + 1) * 4 + kg];
-            mma(B0, off0, false, ks);
-            loadB(B0, ks + 2);
-            off0 = koff[(ks + 2) * 4 + kg];
-            mma(B1, off1, false, ks + 1);
+        for (int m = 0; m < M; ++m) {
+            A[m].q = *reinterpret_cast<const uint4*>(abase + m * zstride + off);
+            if (pad_step) A[m].q = ok ? A[m].q : uint4{0u, 0u, 0u, 0u};
         }
-        if (ks + 1 < nsteps) {
-            loadB(B1, ks + 1);
-            off1 = koff[(ks + 1) * 4 + kg];
-            mma(B0, off0, false, ks);
-            mma(B1, off1, true, ks + 1);
-        } else if (ks < nsteps) {
-            mma(B0, off0, true, ks);
-        }
-    } else {
-        // from 2 output tiles on: the weight fragments and halo offsets of the
-        // next P steps are in flight while a step runs its NT x TZ MFMAs, and the
-        // K-padding select runs on every step (one tile: two steps per trip with
-        // alternating buffers and the padding step peeled, faster there --
-        // measured 136 against 147-154 us for the 32-channel 128^3 layers)
-        constexpr int P = NT == 2 ? 3 : 2;
-        auto loadB = [&](Frag (&b)[NT], int ks) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
-                b[t].q = *reinterpret_cast<const uint4*>(bbase + (size_t)t * 16 * a.Kp + ks * 32);
-        };
-        auto mma = [&](const Frag (&b)[NT], int off, int ks) {
-            const bool ok = ks < nsteps - 1 || (ks * 32 + 8 * kg) < 27 * cin;
-            Frag A[kTZ];
+        for (int m = 0; m < M; ++m)
 #pragma unroll
-            for (int m = 0; m < kTZ; ++m) {
-                A[m].q = *reinterpret_cast<const uint4*>(abase + m * mstride + off);
-                A[m].q = ok ? A[m].q : uint4{0u, 0u, 0u, 0u};
-            }
+            for (int t = 0; t < NW; ++t)
+                acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[t].v, A[m].v, acc[m][t], 0, 0, 0);
+    };
+    // the weight fragments and halo offsets of the next P steps are in flight
+    // while a step runs its MFMAs
+    constexpr int P = NW == 2 ? 3 : 2;
+    Frag Bq[P][NW];
+    int offq[P];
 #pragma unroll
-            for (int m = 0; m < kTZ; ++m)
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[m].v, b[t].v, acc[m][t], 0, 0, 0);
-        };
-        Frag Bq[P][NT];
-        int offq[P];
+    for (int p = 0; p < P; ++p) {
+        offq[p] = p < nsteps ? koff[p * 4 + kg] : 0;
+        if (p < nsteps) loadB(Bq[p], p);
+    }
+    int ks0 = 0;
+    for (; ks0 + 2 * P < nsteps; ks0 += P) {
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            offq[p] = p < nsteps ? koff[p * 4 + kg] : 0;
-            if (p < nsteps) loadB(Bq[p], p);
+            mma(Bq[p], offq[p], false, ks0 + p);
+            loadB(Bq[p], ks0 + p + P);
+            offq[p] = koff[(ks0 + p + P) * 4 + kg];
         }
-        for (int ks0 = 0; ks0 < nsteps; ks0 += P) {
+    }
+    for (; ks0 < nsteps; ks0 += P) {
 #pragma unroll
-            for (int p = 0; p < P; ++p) {
-                const int ks = ks0 + p;
-                if (ks < nsteps) {
-                    mma(Bq[p], offq[p], ks);
-                    if (ks + P < nsteps) {
-                        loadB(Bq[p], ks + P);
-                        offq[p] = koff[(ks + P) * 4 + kg];
-                    }
+        for (int p = 0; p < P; ++p) {
+            const int ks = ks0 + p;
+            if (ks < nsteps) {
+                mma(Bq[p], offq[p], ks == nsteps - 1, ks);
+                if (ks + P < nsteps) {
+                    loadB(Bq[p], ks + P);
+                    offq[p] = koff[(ks + P) * 4 + kg];
                 }
             }
         }
     }
-    // epilogue: output row 4 kg + i of tile m is voxel (x0 + 4 kg + i, y0 + wave, z0 + m)
-    const int y = y0 + wave;
+    // epilogue: rows 4 kg .. 4 kg + 3 of column r are four channels of voxel x0 + r
+    conv_epilogue(a, acc, 0, kg, [&](int m) {
+        const int z = z0 + m, y = y0 + wave;
+        return x0 + r < a.W && y < a.H && z < a.D ? (z * a.H + y) * a.W + x0 + r : -1;
+    });
+}
+
+// 3x3x3 convolution of CIN = 32, 64, 96 or 128 input channels, one plane of the
+// halo at a time: the taps run plane by plane (dz = -1, 0, 1), so a workgroup that
+// computes 16 x 4 x 1 output voxels and NT tiles of 16 channels needs one
+// 18 x 6 x 1 plane in LDS, and loads the next one into registers while it works.
+// For many channels (a whole halo does not fit) and for small grids (where the
+// whole-halo kernel's blocks leave compute units idle).  K order, waves and
+// operands as in k_conv_fwd_tile.  What bounds it: the weights' reads through L1.
+// 128 -> 64 channels at 32^3: gathered from global memory 99 us, here 51; 128 ->
+// 128 at 16^3 60 -> 29 us; 64 -> 64 at 32^3 26 us with whole halos, 20 here.
+template <int NT, int WN, int CIN>
+__global__ __launch_bounds__(256) void k_conv_fwd_planes(ConvFwd a, int ncb)
+{
+    constexpr int NW = NT / WN, CC = CIN / 32, S = 9 * CC, G = CIN / 8;
+    constexpr int kItems = kHX * kHY * G, kStage = (kItems + 255) / 256;
+    __shared__ uint4 hs4[kHX * kHY * G];                   // [kHY][kHX][G], swizzled
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, kg = lane >> 4;
+    const int3 blk = xcd_block();
+    const int x0 = blk.x / ncb * kTX, y0 = blk.y * kTY, z = blk.z;
+    const int wy = wave / WN * WN;
+    const int c16 = (blk.x % ncb * NT + wave % WN * NW) * 16;
+    uint4 q[kStage];
+    auto fetch = [&](int dz) {
 #pragma unroll
-    for (int m = 0; m < kTZ; ++m)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int co = t * 16 + r;
-            if (co >= a.cout) continue;
-            const int z = z0 + m;
-            if (z >= a.D || y >= a.H) continue;
-            const float b = a.bias ? a.bias[co] : 0.0f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int x = x0 + 4 * kg + i;
-                if (x >= a.W) continue;
-                const size_t v = ((size_t)z * a.H + y) * a.W + x;
-                float val = acc[m][t][i] + b;
-                if (a.relu) val = fmaxf(val, 0.0f);
-                if (co < a.split) {
-                    const size_t o = v * a.split + co;
-                    if (a.out_f32) reinterpret_cast<float*>(a.out)[o] = val;
-                    else reinterpret_cast<u16*>(a.out)[o] = f2bf(val);
-                } else {
-                    const int c2 = a.cout - a.split;
-                    const size_t o = v * c2 + (co - a.split);
-                    if (a.out_f32) reinterpret_cast<float*>(a.out2)[o] = val;
-                    else reinterpret_cast<u16*>(a.out2)[o] = f2bf(val);
-                }
-            }
+        for (int j = 0; j < kStage; ++j) {
+            const int i = min((int)threadIdx.x + 256 * j, kItems - 1), vox = i / G;
+            q[j] = conv_input(a, x0 + vox % kHX - 1, y0 + vox / kHX - 1, z + dz, i % G * 8);
         }
+    };
+    f32x4 acc[WN][NW];
+#pragma unroll
+    for (int m = 0; m < WN; ++m)
+#pragma unroll
+        for (int t = 0; t < NW; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // lane bases of the fragments, as in k_conv_fwd_tile
+    const int vb = wy * kHX + r;
+    constexpr int kBases = CIN % 64 ? 4 : 8;
+    int base[kBases];
+#pragma unroll
+    for (int i = 0; i < kBases; ++i) base[i] = vb * G + ((kg + i / 4 * 4) ^ conv_swizzle<CIN>(vb + i % 4));
+    const unsigned boff = (unsigned)(r * a.Kp + 8 * kg);
+    constexpr int P = 3;                                   // divides S
+    Frag Bq[P][NW];
+    auto loadB = [&](Frag (&b)[NW], int ks) {
+#pragma unroll
+        for (int t = 0; t < NW; ++t)
+            b[t].q = *reinterpret_cast<const uint4*>(a.wt + (size_t)(c16 + t * 16) * a.Kp + ks * 32 + boff);
+    };
+    fetch(-1);
+#pragma unroll
+    for (int p = 0; p < P; ++p) loadB(Bq[p], p);
+    for (int dz = 0; dz < 3; ++dz) {
+        if (dz) __syncthreads();                           // the plane before is consumed
+#pragma unroll
+        for (int j = 0; j < kStage; ++j) {
+            const int i = min((int)threadIdx.x + 256 * j, kItems - 1);
+            hs4[i / G * G + (i % G ^ conv_swizzle<CIN>(i / G))] = q[j];
+        }
+        __syncthreads();
+        if (dz < 2) fetch(dz);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int tv = s / CC / 3 * kHX + s / CC % 3, ck = s % CC;
+            Frag A[WN];
+#pragma unroll
+            for (int m = 0; m < WN; ++m) {
+                const int c = tv + m * kHX;
+                A[m].q = hs4[base[c % 4 + (kBases == 8 ? ck % 2 * 4 : 0)] + c * G + (kBases == 8 ? ck / 2 * 8 : ck * 4)];
+            }
+#pragma unroll
+            for (int m = 0; m < WN; ++m)
+#pragma unroll
+                for (int t = 0; t < NW; ++t)
+                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Bq[s % P][t].v, A[m].v, acc[m][t], 0, 0, 0);
+            loadB(Bq[s % P], min(dz * S + s + P, 3 * S - 1));
+        }
+    }
+    conv_epilogue(a, acc, c16, kg, [&](int m) {
+        const int y = y0 + wy + m;
+        return x0 + r < a.W && y < a.H ? (z * a.H + y) * a.W + x0 + r : -1;
+    });
 }
 
 // 3x3x3 convolution of a single input channel (the network's input layer),
 // up to 16 output channels: 27 MACs per output channel, so FP32 FMAs on the
 // BF16 values (their products are exact in FP32) instead of MFMAs whose K
 // values would each be a separately gathered tap.  A workgroup stages the
-// 18 x 6 x 6 input halo of a 16 x 4 x 4 output block in LDS; each thread
-// computes one output voxel's channels.  The weights are the same for every
-// lane (read with uniform addresses, so they arrive through scalar loads).
+// input halo of a 16 x 4 x 4 VZ output block in LDS; each thread computes the
+// channels of VZ output voxels along z.
+//
+// What bounds it: the FMAs, and the weights' loads and conversions to FP32, which
+// VZ voxels share: 16 channels of 128^3 voxels 68 -> 50 us with VZ = 4.
+template <int VZ>
 __global__ __launch_bounds__(256) void k_conv_fwd_c1(ConvFwd a)
 {
-    __shared__ float halo[6][6][18];
-    const int x0 = blockIdx.x * 16, y0 = blockIdx.y * 4, z0 = blockIdx.z * 4;
+    constexpr int kHZ = 4 * VZ + 2;
+    __shared__ float halo[kHZ][6][18];
+    const int x0 = blockIdx.x * 16, y0 = blockIdx.y * 4, z0 = blockIdx.z * 4 * VZ;
     const int Hin = a.H >> a.up, Win = a.W >> a.up;
-    for (int i = threadIdx.x; i < 18 * 6 * 6; i += 256) {
+#pragma unroll 4
+    for (int i = threadIdx.x; i < 18 * 6 * kHZ; i += 256) {
         const int hx = i % 18, hy = (i / 18) % 6, hz = i / 108;
         const int x = x0 + hx - 1, y = y0 + hy - 1, z = z0 + hz - 1;
         const bool ok = (unsigned)x < (unsigned)a.W && (unsigned)y < (unsigned)a.H && (unsigned)z < (unsigned)a.D;
-        halo[hz][hy][hx] =
-            ok ? bf2f(a.in0[((size_t)(z >> a.up) * Hin + (y >> a.up)) * Win + (x >> a.up)]) : 0.0f;
+        const size_t src = ((size_t)(z >> a.up) * Hin + (y >> a.up)) * Win + (x >> a.up);
+        const u16 v = a.in0[ok ? src : 0];
+        halo[hz][hy][hx] = ok ? bf2f(v) : 0.0f;
     }
     __syncthreads();
-    const int tx = threadIdx.x & 15, ty = (threadIdx.x >> 4) & 3, tz = threadIdx.x >> 6;
-    const int x = x0 + tx, y = y0 + ty, z = z0 + tz;
-    if (x >= a.W || y >= a.H || z >= a.D) return;
-    float v[27];
+    const int tx = threadIdx.x & 15, ty = (threadIdx.x >> 4) & 3, tz = (threadIdx.x >> 6) * VZ;
+    const int x = x0 + tx, y = y0 + ty;
+    if (x >= a.W || y >= a.H) return;
+    float v[VZ + 2][9];
 #pragma unroll
-    for (int t = 0; t < 27; ++t) v[t] = halo[tz + t / 9][ty + (t / 3) % 3][tx + t % 3];
-    const size_t vox = ((size_t)z * a.H + y) * a.W + x;
-    float out[16];
+    for (int p = 0; p < VZ + 2; ++p)
 #pragma unroll
-    for (int co = 0; co < 16; ++co) {
-        if (co >= a.cout) {
-            out[co] = 0.0f;
-            continue;
+        for (int t = 0; t < 9; ++t) v[p][t] = halo[tz + p][ty + t / 3][tx + t % 3];
+    const size_t vox = ((size_t)(z0 + tz) * a.H + y) * a.W + x, plane = (size_t)a.H * a.W;
+    // one voxel's 16 BF16 channels leave as two 16-byte stores
+    const bool whole = !a.out_f32 && a.split == 16 && a.cout == 16 && (reinterpret_cast<uintptr_t>(a.out) & 15) == 0;
+    unsigned packed[VZ][8];
+#pragma unroll
+    for (int c2 = 0; c2 < 8; ++c2) {
+        float out[2][VZ];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int co = min(2 * c2 + h, a.cout - 1);    // past the last: repeated, not stored
+            const u16* wr = a.wt + (size_t)co * a.Kp;
+#pragma unroll
+            for (int j = 0; j < VZ; ++j) out[h][j] = 0.0f;
+#pragma unroll
+            for (int t = 0; t < 27; ++t) {
+                const float w = bf2f(wr[t]);
+#pragma unroll
+                for (int j = 0; j < VZ; ++j) out[h][j] = fmaf(w, v[j + t / 9][t % 9], out[h][j]);
+            }
+            const float b = a.bias ? a.bias[co] : 0.0f;
+#pragma unroll
+            for (int j = 0; j < VZ; ++j) {
+                out[h][j] += b;
+                if (a.relu) out[h][j] = fmaxf(out[h][j], 0.0f);
+            }
+            if (!whole && 2 * c2 + h < a.cout) {
+                const bool first = co < a.split;
+                const int st = first ? a.split : a.cout - a.split, c = first ? co : co - a.split;
+                void* dst = first ? a.out : a.out2;
+#pragma unroll
+                for (int j = 0; j < VZ; ++j) {
+                    if (z0 + tz + j >= a.D) continue;
+                    const size_t o = (vox + j * plane) * st + c;
+                    if (a.out_f32) reinterpret_cast<float*>(dst)[o] = out[h][j];
+                    else reinterpret_cast<u16*>(dst)[o] = (u16)f2bf2(out[h][j], 0.0f);
+                }
+            }
         }
-        const u16* wr = a.wt + (size_t)co * a.Kp;
-        float acc = 0.0f;
 #pragma unroll
-        for (int t = 0; t < 27; ++t) acc = fmaf(bf2f(wr[t]), v[t], acc);
-        acc += a.bias ? a.bias[co] : 0.0f;
-        out[co] = a.relu ? fmaxf(acc, 0.0f) : acc;
+        for (int j = 0; j < VZ; ++j) packed[j][c2] = f2bf2(out[0][j], out[1][j]);
     }
-    if (!a.out_f32 && a.split == 16 && a.cout == 16) {
-        // one voxel's 16 BF16 channels: two 16-byte stores
-        Frag lo, hi;
+    if (!whole) return;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            lo.h[j] = f2bf(out[j]);
-            hi.h[j] = f2bf(out[8 + j]);
-        }
-        uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<u16*>(a.out) + vox * 16);
-        dst[0] = lo.q;
-        dst[1] = hi.q;
-        return;
-    }
-    for (int co = 0; co < 16; ++co) {
-        if (co >= a.cout) break;
-        if (co < a.split) {
-            const size_t o = vox * a.split + co;
-            if (a.out_f32) reinterpret_cast<float*>(a.out)[o] = out[co];
-            else reinterpret_cast<u16*>(a.out)[o] = f2bf(out[co]);
-        } else {
-            const size_t o = vox * (a.cout - a.split) + (co - a.split);
-            if (a.out_f32) reinterpret_cast<float*>(a.out2)[o] = out[co];
-            else reinterpret_cast<u16*>(a.out2)[o] = f2bf(out[co]);
-        }
+    for (int j = 0; j < VZ; ++j) {
+        if (z0 + tz + j >= a.D) continue;
+        uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<u16*>(a.out) + (vox + j * plane) * 16);
+        dst[0] = uint4{packed[j][0], packed[j][1], packed[j][2], packed[j][3]};
+        dst[1] = uint4{packed[j][4], packed[j][5], packed[j][6], packed[j][7]};
     }
 }
 
@@ -890,7 +1183,7 @@ hipError_t wgrad_c1(const ConvWgrad& a, hipStream_t s)
 // channels in registers (16-byte loads), then waves and the workgroup combine
 // them, one atomic per channel and workgroup.
 template <int CIN>
-__global__ __launch_bounds__(256) void k_wgrad_1x1_out1(ConvWgrad a, size_t nvox)
+__global__ __launch_bounds__(kSumBlock) void k_wgrad_1x1_out1(ConvWgrad a, size_t nvox)
 {
     __shared__ float red[CIN];
     if (threadIdx.x < CIN) red[threadIdx.x] = 0.0f;
@@ -898,7 +1191,7 @@ __global__ __launch_bounds__(256) void k_wgrad_1x1_out1(ConvWgrad a, size_t nvox
     float sum[CIN];
 #pragma unroll
     for (int c = 0; c < CIN; ++c) sum[c] = 0.0f;
-    for (size_t v = (size_t)blockIdx.x * 256 + threadIdx.x; v < nvox; v += (size_t)gridDim.x * 256) {
+    for (size_t v = (size_t)blockIdx.x * kSumBlock + threadIdx.x; v < nvox; v += (size_t)gridDim.x * kSumBlock) {
         const float g = bf2f(a.dy[v]);
         const u16* x = a.in0 + v * CIN;
 #pragma unroll
@@ -1072,7 +1365,7 @@ __global__ void k_relu_mask_pc(const float* __restrict__ dout, const u16* __rest
 // channels (8 t + j) mod C through the grid-stride loop: the 8 sums stay in
 // registers, lanes holding the same channels are combined with wave
 // shuffles, and the rest reach LDS once per wave.
-__global__ __launch_bounds__(256) void k_relu_mask_v8(const float* __restrict__ dout, const u16* __restrict__ out,
+__global__ __launch_bounds__(kSumBlock) void k_relu_mask_v8(const float* __restrict__ dout, const u16* __restrict__ out,
                                                       int relu, u16* __restrict__ g, float* __restrict__ dbias,
                                                       size_t n8, int C)
 {
@@ -1144,10 +1437,10 @@ __global__ void k_relu_mask(const float* __restrict__ dout, const u16* __restric
 
 // Loss 1/V sum (x - t)^2 of the network output (FP32) against the target,
 // and its gradient through the final ReLU.
-__global__ void k_mse(const float* __restrict__ x, const float* __restrict__ t, float* __restrict__ g,
+__global__ __launch_bounds__(kSumBlock) void k_mse(const float* __restrict__ x, const float* __restrict__ t, float* __restrict__ g,
                       double* __restrict__ loss, size_t n)
 {
-    __shared__ double red[4];
+    __shared__ double red[kSumBlock / 64];
     double s = 0.0;
     const float inv = 1.0f / (float)n;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
@@ -1159,7 +1452,11 @@ __global__ void k_mse(const float* __restrict__ x, const float* __restrict__ t, 
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0) unsafeAtomicAdd(loss, (red[0] + red[1] + red[2] + red[3]) / (double)n);
+    if (threadIdx.x == 0) {
+        s = 0.0;
+        for (unsigned w = 0; w < blockDim.x / 64; ++w) s += red[w];
+        unsafeAtomicAdd(loss, s / (double)n);
+    }
 }
 
 // Adam on FP32 master weights (bias-corrected), gradients cleared after use.
@@ -1179,13 +1476,21 @@ __global__ void k_adam(float* __restrict__ w, float* __restrict__ g, float* __re
 }
 
 // Network input: A^T y scaled by 1 / max (max over the volume), as BF16.
-__global__ void k_absmax(const float* __restrict__ x, size_t n, unsigned int* __restrict__ out)
+__global__ __launch_bounds__(kSumBlock) void k_absmax(const float* __restrict__ x, size_t n,
+                                                      unsigned int* __restrict__ out)
 {
+    __shared__ float red[kSumBlock / 64];
     float mval = 0.0f;
+#pragma unroll 4
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         mval = fmaxf(mval, fabsf(x[i]));
     for (int o = 32; o > 0; o >>= 1) mval = fmaxf(mval, __shfl_xor(mval, o));
-    if ((threadIdx.x & 63) == 0) atomicMax(out, __float_as_uint(mval));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mval;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (unsigned w = 1; w < blockDim.x / 64; ++w) mval = fmaxf(mval, red[w]);
+        atomicMax(out, __float_as_uint(mval));
+    }
 }
 
 __global__ void k_scale_to_bf16(const float* __restrict__ x, const unsigned int* __restrict__ mx,
@@ -1249,6 +1554,17 @@ hipError_t conv_nt(const ConvFwd& a, int nt, hipStream_t s)
     }
 }
 
+template <int CIN>
+hipError_t conv_planes(const ConvFwd& a, int nt, int ncb, dim3 g, hipStream_t s)
+{
+    switch (nt) {
+    case 1: hipLaunchKernelGGL((k_conv_fwd_planes<1, 1, CIN>), g, dim3(256), 0, s, a, ncb); break;
+    case 2: hipLaunchKernelGGL((k_conv_fwd_planes<2, 2, CIN>), g, dim3(256), 0, s, a, ncb); break;
+    default: hipLaunchKernelGGL((k_conv_fwd_planes<4, 4, CIN>), g, dim3(256), 0, s, a, ncb); break;
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t nn_conv_fwd(const ConvFwd& a, int ks, hipStream_t s)
@@ -1257,36 +1573,67 @@ hipError_t nn_conv_fwd(const ConvFwd& a, int ks, hipStream_t s)
     const int ntp = nt <= 1 ? 1 : (nt <= 2 ? 2 : (nt <= 4 ? 4 : 8));
     const int cin = a.c0 + a.c1;
     const bool cin1 = cin == 1;
+    if (ks == 3 && cin % 32 == 0 && cin <= 128 && a.D < 65536) {
+        const int tz = cin <= 32 ? 4 : 2;
+        const size_t plane = (size_t)((a.W + kTX - 1) / kTX) * ((a.H + kTY - 1) / kTY);
+        // fewer than two whole-halo workgroups per compute unit (with eight channel
+        // tiles, fewer than one: 64 -> 128 channels at 32^3 are 35 us by planes, 33
+        // with whole halos)
+        const size_t blocks = plane * ((a.D + tz - 1) / tz);
+        if (cin > 64 || blocks < 256 || (blocks < 512 && ntp <= 4)) {
+            // channel tiles per workgroup: as many as leave two workgroups per
+            // compute unit
+            int nt = std::min(ntp, 4);
+            while (nt > 1 && plane * a.D * (ntp / nt) < 512) nt /= 2;
+            const dim3 g((a.W + kTX - 1) / kTX * (ntp / nt), (a.H + kTY - 1) / kTY, a.D);
+            return cin == 32   ? conv_planes<32>(a, nt, ntp / nt, g, s)
+                   : cin == 64 ? conv_planes<64>(a, nt, ntp / nt, g, s)
+                   : cin == 96 ? conv_planes<96>(a, nt, ntp / nt, g, s)
+                               : conv_planes<128>(a, nt, ntp / nt, g, s);
+        }
+    }
     if (ks == 3 && cin >= 8 && cin <= 64 && cin % 8 == 0) {
         // 8 output planes per workgroup up to 16 channels (35 KiB halo), 4 up to 32
         // (41 KiB), 2 up to 64 (55 KiB)
         const int tz = (cin <= 16 && ntp <= 4) ? 8 : (cin <= 32 ? 4 : 2);
         const dim3 g((a.W + kTX - 1) / kTX, (a.H + kTY - 1) / kTY, (a.D + tz - 1) / tz);
-        // the halo, then the per-step offset table (nsteps x 4 ints)
-        const size_t lds = (size_t)kHX * kHY * (tz + 2) * cin * sizeof(unsigned short) +
-                           (size_t)(a.Kp / 32) * 4 * sizeof(int);
-        if (tz == 8) {
-            switch (ntp) {
-            case 1: hipLaunchKernelGGL((k_conv_fwd_lds<1, 8>), g, dim3(256), lds, s, a); break;
-            case 2: hipLaunchKernelGGL((k_conv_fwd_lds<2, 8>), g, dim3(256), lds, s, a); break;
-            case 4: hipLaunchKernelGGL((k_conv_fwd_lds<4, 8>), g, dim3(256), lds, s, a); break;
-            default: return hipErrorInvalidValue;   // tz = 8 is chosen only for ntp <= 4
-            }
-        } else if (tz == 4) {
-            switch (ntp) {
-            case 1: hipLaunchKernelGGL((k_conv_fwd_lds<1, 4>), g, dim3(256), lds, s, a); break;
-            case 2: hipLaunchKernelGGL((k_conv_fwd_lds<2, 4>), g, dim3(256), lds, s, a); break;
-            case 4: hipLaunchKernelGGL((k_conv_fwd_lds<4, 4>), g, dim3(256), lds, s, a); break;
-            default: hipLaunchKernelGGL((k_conv_fwd_lds<8, 4>), g, dim3(256), lds, s, a); break;
-            }
-        } else {
-            switch (ntp) {
-            case 1: hipLaunchKernelGGL((k_conv_fwd_lds<1, 2>), g, dim3(256), lds, s, a); break;
-            case 2: hipLaunchKernelGGL((k_conv_fwd_lds<2, 2>), g, dim3(256), lds, s, a); break;
-            case 4: hipLaunchKernelGGL((k_conv_fwd_lds<4, 2>), g, dim3(256), lds, s, a); break;
-            default: hipLaunchKernelGGL((k_conv_fwd_lds<8, 2>), g, dim3(256), lds, s, a); break;
+        const size_t halo = (size_t)kHX * kHY * (tz + 2) * cin * sizeof(unsigned short);
+#define LTM_TILE(CIN, NT, TZ, WN) \
+    hipLaunchKernelGGL((k_conv_fwd_tile<CIN, NT, TZ, WN>), g, dim3(256), halo, s, a); break
+        switch (cin * 16 + ntp) {
+        case 16 * 16 + 1: LTM_TILE(16, 1, 8, 1);
+        case 16 * 16 + 2: LTM_TILE(16, 2, 8, 1);
+        case 16 * 16 + 4: LTM_TILE(16, 4, 8, 1);
+        case 16 * 16 + 8: LTM_TILE(16, 8, 4, 2);
+        case 32 * 16 + 1: LTM_TILE(32, 1, 4, 1);
+        case 32 * 16 + 2: LTM_TILE(32, 2, 4, 2);
+        case 32 * 16 + 4: LTM_TILE(32, 4, 4, 4);
+        case 32 * 16 + 8: LTM_TILE(32, 8, 4, 2);
+        case 64 * 16 + 1: LTM_TILE(64, 1, 2, 1);
+        case 64 * 16 + 2: LTM_TILE(64, 2, 2, 2);
+        case 64 * 16 + 4: LTM_TILE(64, 4, 2, 2);
+        case 64 * 16 + 8: LTM_TILE(64, 8, 2, 4);
+        default: {
+            // the halo, then the per-step offset table (nsteps x 4 ints)
+            const size_t lds = halo + (size_t)(a.Kp / 32) * 4 * sizeof(int);
+#define LTM_CONV(NT, TZ) hipLaunchKernelGGL((k_conv_fwd_lds<NT, TZ>), g, dim3(256), lds, s, a); break
+            switch (tz * 16 + ntp) {
+            case 8 * 16 + 1: LTM_CONV(1, 8);
+            case 8 * 16 + 2: LTM_CONV(2, 8);
+            case 8 * 16 + 4: LTM_CONV(4, 8);
+            case 4 * 16 + 1: LTM_CONV(1, 4);
+            case 4 * 16 + 2: LTM_CONV(2, 4);
+            case 4 * 16 + 4: LTM_CONV(4, 4);
+            case 4 * 16 + 8: LTM_CONV(8, 4);
+            case 2 * 16 + 1: LTM_CONV(1, 2);
+            case 2 * 16 + 2: LTM_CONV(2, 2);
+            case 2 * 16 + 4: LTM_CONV(4, 2);
+            default: LTM_CONV(8, 2);
             }
         }
+        }
+#undef LTM_TILE
+#undef LTM_CONV
         return hipGetLastError();
     }
     if (ks == 1 && a.cout == 1 && a.c1 == 0 && !a.up && (cin == 8 || cin == 16 || cin == 32)) {
@@ -1298,8 +1645,12 @@ hipError_t nn_conv_fwd(const ConvFwd& a, int ks, hipStream_t s)
         return hipGetLastError();
     }
     if (ks == 3 && cin1 && a.c1 == 0 && a.cout <= 16) {
-        const dim3 g((a.W + 15) / 16, (a.H + 3) / 4, (a.D + 3) / 4);
-        hipLaunchKernelGGL(k_conv_fwd_c1, g, dim3(256), 0, s, a);
+        // four voxels per thread while that leaves two workgroups per compute unit
+        const dim3 g((a.W + 15) / 16, (a.H + 3) / 4, (a.D + 15) / 16);
+        if ((size_t)g.x * g.y * g.z >= 512)
+            hipLaunchKernelGGL(k_conv_fwd_c1<4>, g, dim3(256), 0, s, a);
+        else
+            hipLaunchKernelGGL(k_conv_fwd_c1<1>, dim3(g.x, g.y, (a.D + 3) / 4), dim3(256), 0, s, a);
         return hipGetLastError();
     }
     if (ks == 3) return cin1 ? conv_nt<3, true>(a, ntp, s) : conv_nt<3, false>(a, ntp, s);
@@ -1323,10 +1674,10 @@ hipError_t nn_conv_wgrad(const ConvWgrad& a, int ks, hipStream_t s)
     }
     if (ks == 1 && a.cout == 1 && a.c1 == 0 && !a.up && a.K == cin && (cin == 8 || cin == 16 || cin == 32)) {
         const size_t nvox = (size_t)a.D * a.H * a.W;
-        const dim3 g(std::min(nblocks(nvox), 1024u));
-        if (cin == 8) hipLaunchKernelGGL((k_wgrad_1x1_out1<8>), g, dim3(256), 0, s, a, nvox);
-        else if (cin == 16) hipLaunchKernelGGL((k_wgrad_1x1_out1<16>), g, dim3(256), 0, s, a, nvox);
-        else hipLaunchKernelGGL((k_wgrad_1x1_out1<32>), g, dim3(256), 0, s, a, nvox);
+        const dim3 g(sum_blocks(nvox));
+        if (cin == 8) hipLaunchKernelGGL((k_wgrad_1x1_out1<8>), g, dim3(kSumBlock), 0, s, a, nvox);
+        else if (cin == 16) hipLaunchKernelGGL((k_wgrad_1x1_out1<16>), g, dim3(kSumBlock), 0, s, a, nvox);
+        else hipLaunchKernelGGL((k_wgrad_1x1_out1<32>), g, dim3(kSumBlock), 0, s, a, nvox);
         return hipGetLastError();
     }
     auto lg2 = [](int n) { int l = 0; while ((1 << l) < n) ++l; return (1 << l) == n ? l : -1; };
@@ -1390,13 +1741,13 @@ hipError_t nn_sumpool(const float* dh, float* dl, int D, int H, int W, int C, in
 hipError_t nn_relu_mask(const float* dout, const unsigned short* out, int relu, unsigned short* g,
                         float* dbias, size_t n, int C, hipStream_t s)
 {
-    // at most 1024 workgroups: each adds C partial sums into dbias with
-    // global atomics, which contend on the C addresses
+    // at most one workgroup per compute unit: each adds C partial sums into dbias
+    // with global atomics, which contend on the C addresses
     const bool pow2 = C >= 1 && (C & (C - 1)) == 0;
     const bool aligned = ((reinterpret_cast<uintptr_t>(dout) | reinterpret_cast<uintptr_t>(out) |
                            reinterpret_cast<uintptr_t>(g)) & 15) == 0;
     if (pow2 && C <= 2048 && n % 8 == 0 && aligned) {   // C divides the grid stride in elements (2048 k)
-        hipLaunchKernelGGL(k_relu_mask_v8, dim3(std::min(nblocks(n / 8), 1024u)), dim3(256), C * sizeof(float), s,
+        hipLaunchKernelGGL(k_relu_mask_v8, dim3(sum_blocks(n / 8)), dim3(kSumBlock), C * sizeof(float), s,
                            dout, out, relu, g, dbias, n / 8, C);
         return hipGetLastError();
     }
@@ -1410,8 +1761,7 @@ hipError_t nn_relu_mask(const float* dout, const unsigned short* out, int relu, 
 
 hipError_t nn_mse(const float* x, const float* t, float* g, double* loss, size_t n, hipStream_t s)
 {
-    // at most 1024 workgroups: each adds its partial loss with one FP64 atomic
-    hipLaunchKernelGGL(k_mse, dim3(std::min(nblocks(n), 1024u)), dim3(256), 0, s, x, t, g, loss, n);
+    hipLaunchKernelGGL(k_mse, dim3(sum_blocks(n)), dim3(kSumBlock), 0, s, x, t, g, loss, n);
     return hipGetLastError();
 }
 
@@ -1426,7 +1776,7 @@ hipError_t nn_adam(float* w, float* g, float* m, float* v, size_t n, float lr, f
 hipError_t nn_prep_input(const float* x, unsigned short* y, unsigned int* scratch, size_t n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, scratch, (size_t)1, 0u);
-    hipLaunchKernelGGL(k_absmax, dim3(std::min(nblocks(n), 1024u)), dim3(256), 0, s, x, n, scratch);
+    hipLaunchKernelGGL(k_absmax, dim3(sum_blocks(n)), dim3(kSumBlock), 0, s, x, n, scratch);
     hipLaunchKernelGGL(k_scale_to_bf16, dim3(nblocks(n)), dim3(256), 0, s, x, scratch, y, n);
     return hipGetLastError();
 }
