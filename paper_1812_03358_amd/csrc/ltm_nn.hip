@@ -232,6 +232,12 @@ __device__ __forceinline__ uint4 load_or_zero(const u16* p, bool ok)
     return uint4{q.x, q.y, q.z, q.w};
 }
 
+__device__ __forceinline__ u16 load_or_zero16(const u16* p, bool ok)
+{
+    typedef const __attribute__((address_space(1))) u16* GlobalPtr;
+    return *(ok ? (GlobalPtr)p : (GlobalPtr)kZeroVoxel);
+}
+
 // The 8 channels [ci, ci + 8) of input voxel (x, y, z) on the output grid (the
 // upsampled and the concatenated inputs resolved), zero outside the grid.
 __device__ __forceinline__ uint4 conv_input(const ConvFwd& a, int x, int y, int z, int ci)
@@ -885,8 +891,8 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_pow2(ConvWgrad a, int lw, in
     }
 }
 
-// Weight gradient of a 3x3x3 convolution for rows whose width is a multiple
-// of XC (32, 64 or 128) voxels and Cin, Cout multiples of 16.  A tap's x shift
+// Weight gradient of a 3x3x3 convolution in chunks of XC (32, 64 or 128) voxels
+// of a row (the last one zero past the row's end), Cin and Cout multiples of 16.  A tap's x shift
 // is moved from the input onto dY: sum_x dY[x] X[x + dx] = sum_x' dY[x' - dx]
 // X[x'], each input position x' paired by the unit that holds it.  A unit is
 // XC voxels (chunk) of one output row (z, y).  Per unit a workgroup holds in
@@ -912,7 +918,7 @@ struct WgradStage {
     Frag f[NDI];
 };
 
-template <int XC>
+template <int XC, bool kRagged>
 __device__ __forceinline__ void wgrad_load(const ConvWgrad& a, int cit, int cot, int z, int y, int x0, bool full,
                                            WgradStage<XC>& st)
 {
@@ -927,17 +933,20 @@ __device__ __forceinline__ void wgrad_load(const ConvWgrad& a, int cit, int cot,
         const int zz = z + dzi - 1, yy = y + k - 1;
         const int ci = cit * 16 + g * 8;
         const int xb = x0 + x8 * 8;
+        auto voxel = [&](const u16* p, int x) {
+            return !kRagged ? *reinterpret_cast<const uint4*>(p) : load_or_zero(p, x < a.W);
+        };
         if (i < nitems && (unsigned)zz < (unsigned)a.D && (unsigned)yy < (unsigned)a.H) {
             if (ci < a.c0) {
                 const u16* src = a.in0 + ((size_t)(zz >> a.up) * Hin + (yy >> a.up)) * Win * a.c0 + ci;
 #pragma unroll
                 for (int jx = 0; jx < 8; ++jx)
-                    st.q[it][jx].q = *reinterpret_cast<const uint4*>(src + (size_t)((xb + jx) >> a.up) * a.c0);
+                    st.q[it][jx].q = voxel(src + (size_t)((xb + jx) >> a.up) * a.c0, xb + jx);
             } else {
                 const u16* src = a.in1 + ((size_t)zz * a.H + yy) * a.W * a.c1 + (ci - a.c0);
 #pragma unroll
                 for (int jx = 0; jx < 8; ++jx)
-                    st.q[it][jx].q = *reinterpret_cast<const uint4*>(src + (size_t)(xb + jx) * a.c1);
+                    st.q[it][jx].q = voxel(src + (size_t)(xb + jx) * a.c1, xb + jx);
             }
         } else {
 #pragma unroll
@@ -992,13 +1001,14 @@ __device__ __forceinline__ void wgrad_store(int y, bool full, const WgradStage<X
             const int ix = h + d - 2;
             if ((unsigned)ix < (unsigned)XC) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) dys[(d * 16 + half * 8 + j) * XS + ix] = st.f[it].h[j];
+                for (int j = 0; j < 8; ++j)
+                    dys[(d * 16 + half * 8 + j) * XS + ix] = st.f[it].h[j];
             }
         }
     }
 }
 
-template <int XC>
+template <int XC, bool kRagged>
 __global__ __launch_bounds__(192) void k_conv_wgrad_rows(ConvWgrad a, int nshare)
 {
     constexpr int XS = XC + 8;                   // LDS row stride (elements), padded against bank conflicts
@@ -1010,7 +1020,7 @@ __global__ __launch_bounds__(192) void k_conv_wgrad_rows(ConvWgrad a, int nshare
     const int n_co = a.cout >> 4;
     const int cot = blockIdx.x % n_co, cit = blockIdx.x / n_co;
     const int cin = a.c0 + a.c1;
-    const int chunks = a.W / XC;
+    const int chunks = kRagged ? (a.W + XC - 1) / XC : a.W / XC;
     const int nunits = a.D * chunks * a.H;
     const int u0 = (int)(((long long)nunits * blockIdx.y) / nshare);
     const int u1 = (int)(((long long)nunits * (blockIdx.y + 1)) / nshare);
@@ -1030,7 +1040,7 @@ __global__ __launch_bounds__(192) void k_conv_wgrad_rows(ConvWgrad a, int nshare
     int z, y, x0;
     if (u0 < u1) {
         coords(u0, z, y, x0);
-        wgrad_load<XC>(a, cit, cot, z, y, x0, true, st);
+        wgrad_load<XC, kRagged>(a, cit, cot, z, y, x0, true, st);
     }
     for (int unit = u0; unit < u1; ++unit) {
         const bool full = unit == u0 || y == 0;
@@ -1040,7 +1050,7 @@ __global__ __launch_bounds__(192) void k_conv_wgrad_rows(ConvWgrad a, int nshare
         __syncthreads();
         if (unit + 1 < u1) {
             coords(unit + 1, z, y, x0);
-            wgrad_load<XC>(a, cit, cot, z, y, x0, y == 0, st);
+            wgrad_load<XC, kRagged>(a, cit, cot, z, y, x0, y == 0, st);
         }
         // wave w: dy = w - 1, input row y' = ycur + w - 1 in slot (s, y' mod 3)
         const int ks = (ycur + wave + 2) % 3;
@@ -1079,12 +1089,18 @@ template <int XC>
 hipError_t wgrad_rows(const ConvWgrad& a, hipStream_t s)
 {
     const int tiles = (a.cout / 16) * ((a.c0 + a.c1) / 16);
-    const int units = a.D * a.H * (a.W / XC);
-    // shares of the units per (output tile, input tile) until ~512 workgroups
-    // run (two per CU); each share adds its partial sums into dw
-    const int shares = std::max(1, std::min(units, 512 / tiles));
+    const int units = a.D * a.H * ((a.W + XC - 1) / XC);
+    // shares of the units per (output tile, input tile) until two (rows of 128) or
+    // three workgroups per compute unit run; each share adds its partial sums into
+    // dw.  2, 3 and 5 of them: 16 -> 16 channels at 128^3 80, 114 (2.5) and 110 us (3),
+    // 64 -> 64 at 32^3 82, 68 and 65, 32 -> 64 at 32^3 52, 44 and 48, 64 -> 32 at 64^3 95,
+    // 78 and 95 us: beyond three the adds to one address, one after the other, cost more
     const size_t lds = (size_t)12 * 16 * (XC + 8) * sizeof(u16);
-    hipLaunchKernelGGL((k_conv_wgrad_rows<XC>), dim3(tiles, shares), dim3(192), lds, s, a, shares);
+    const int shares = std::max(1, std::min(units, (XC == 128 ? 512 : 768) / tiles));
+    if (a.W % XC)
+        hipLaunchKernelGGL((k_conv_wgrad_rows<XC, true>), dim3(tiles, shares), dim3(192), lds, s, a, shares);
+    else
+        hipLaunchKernelGGL((k_conv_wgrad_rows<XC, false>), dim3(tiles, shares), dim3(192), lds, s, a, shares);
     return hipGetLastError();
 }
 
@@ -1106,7 +1122,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_c1(ConvWgrad a, int nshare)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, kg = lane >> 4;
     const int cot = blockIdx.x;
-    const int chunks = a.W / XC;
+    const int chunks = (a.W + XC - 1) / XC;
     const int nunits = a.D * a.H * chunks;
     const int u0 = (int)(((long long)nunits * blockIdx.y) / nshare);
     const int u1 = (int)(((long long)nunits * (blockIdx.y + 1)) / nshare);
@@ -1115,31 +1131,46 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_c1(ConvWgrad a, int nshare)
     f32x4 acc[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int unit = u0; unit < u1; ++unit) {
+    // a unit's loads are in flight while the one before is multiplied
+    constexpr int NI = (9 * (XC + 2) + 255) / 256;
+    u16 q[NI];
+    Frag f{};
+    auto load = [&](int unit) {
         const int row = unit / chunks, x0 = (unit - row * chunks) * XC;
         const int z = row / a.H, y = row - z * a.H;
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int i = threadIdx.x + 256 * j, rr = i / (XC + 2), h = i - rr * (XC + 2);
+            const int zz = z + rr / 3 - 1, yy = y + rr % 3 - 1, x = x0 - 1 + h;
+            const bool ok = rr < 9 && (unsigned)zz < (unsigned)a.D && (unsigned)yy < (unsigned)a.H &&
+                            (unsigned)x < (unsigned)a.W;
+            q[j] = load_or_zero16(a.in0 + (ok ? ((size_t)zz * a.H + yy) * a.W + x : 0), ok);
+        }
+        const int x = threadIdx.x >> 1;
+        if (threadIdx.x < XC * 2)
+            f.q = load_or_zero(a.dy + ((size_t)row * a.W + min(x0 + x, a.W - 1)) * a.cout + cot * 16 +
+                                   (threadIdx.x & 1) * 8, x0 + x < a.W);
+    };
+    if (u0 < u1) load(u0);
+    for (int unit = u0; unit < u1; ++unit) {
         __syncthreads();   // the previous unit's fragments are read (and the clears done)
         // input halo x0 - 1 + h: copy d (dx = d - 1) holds X[x0 + i + dx] at i = h - d
-        for (int i = threadIdx.x; i < 9 * (XC + 2); i += 256) {
-            const int rr = i / (XC + 2), h = i - rr * (XC + 2);
-            const int zz = z + rr / 3 - 1, yy = y + rr % 3 - 1, x = x0 - 1 + h;
-            u16 v = 0;
-            if ((unsigned)zz < (unsigned)a.D && (unsigned)yy < (unsigned)a.H && (unsigned)x < (unsigned)a.W)
-                v = a.in0[((size_t)zz * a.H + yy) * a.W + x];
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int i = threadIdx.x + 256 * j, rr = i / (XC + 2), h = i - rr * (XC + 2);
+            if (rr >= 9) continue;
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
                 const int ix = h - d;
-                if ((unsigned)ix < (unsigned)XC) xs[(d * 16 + rr) * XS + ix] = v;
+                if ((unsigned)ix < (unsigned)XC) xs[(d * 16 + rr) * XS + ix] = q[j];
             }
         }
-        for (int i = threadIdx.x; i < XC * 2; i += 256) {
-            const int x = i >> 1, half = i & 1;
-            Frag f;
-            f.q = *reinterpret_cast<const uint4*>(a.dy + ((size_t)row * a.W + x0 + x) * a.cout + cot * 16 + half * 8);
+        if (threadIdx.x < XC * 2) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) dys[(half * 8 + j) * XS + x] = f.h[j];
+            for (int j = 0; j < 8; ++j) dys[((threadIdx.x & 1) * 8 + j) * XS + (threadIdx.x >> 1)] = f.h[j];
         }
         __syncthreads();
+        if (unit + 1 < u1) load(unit + 1);
         for (int gv = wave * 32; gv < XC; gv += 128) {
             Frag A;
             A.q = *reinterpret_cast<const uint4*>(dys + r * XS + gv + 8 * kg);
@@ -1171,9 +1202,10 @@ template <int XC>
 hipError_t wgrad_c1(const ConvWgrad& a, hipStream_t s)
 {
     const int cot = a.cout / 16;
-    const int units = a.D * a.H * (a.W / XC);
-    // shares of the units until ~1024 workgroups run; each adds 16 x 27 sums
-    const int shares = std::max(1, std::min(units, 1024 / cot));
+    const int units = a.D * a.H * ((a.W + XC - 1) / XC);
+    // shares of the units until 512 workgroups run; each adds 16 x 27 sums, one after
+    // the other at each address (128^3: 256 shares 120 us, 512 107, 1024 146)
+    const int shares = std::max(1, std::min(units, 512 / cot));
     hipLaunchKernelGGL((k_conv_wgrad_c1<XC>), dim3(cot, shares), dim3(256), 0, s, a, shares);
     return hipGetLastError();
 }
@@ -1660,14 +1692,23 @@ hipError_t nn_conv_fwd(const ConvFwd& a, int ks, hipStream_t s)
 hipError_t nn_conv_wgrad(const ConvWgrad& a, int ks, hipStream_t s)
 {
     const int cin = a.c0 + a.c1;
-    const int xc = a.W % 128 == 0 ? 128 : a.W % 64 == 0 ? 64 : a.W % 32 == 0 ? 32 : 0;
-    if (ks == 3 && xc && cin % 16 == 0 && a.c0 % 8 == 0 && a.cout % 16 == 0 && a.K == 27 * cin &&
+    auto lg2 = [](int n) { int l = 0; while ((1 << l) < n) ++l; return (1 << l) == n ? l : -1; };
+    const int lw = lg2(a.W), lh = lg2(a.H);
+    const bool pow2 = lw >= 3 && lh >= 0 && (a.W * a.H) % 32 == 0;
+    // the chunk that pads the rows least, the longest of those.  Padding pays: 64 ->
+    // 64 channels at 48 x 48 x 40 gathered voxel by voxel take 823 us, padded 92; only rows of 8 (a
+    // quarter of a chunk) stay with the shift-indexed kernel (rows of 16: 52 us there,
+    // 44 padded, 128 -> 128 channels at 16^3)
+    int xc = 32;
+    for (int c : {64, 128})
+        if ((a.W + c - 1) / c * c <= (a.W + xc - 1) / xc * xc) xc = c;
+    if (ks == 3 && (a.W >= 16 || !pow2) && cin % 16 == 0 && a.c0 % 8 == 0 && a.cout % 16 == 0 && a.K == 27 * cin &&
         (!a.up || (a.W % 2 == 0 && a.H % 2 == 0 && a.D % 2 == 0))) {
         if (xc == 128) return wgrad_rows<128>(a, s);
         if (xc == 64) return wgrad_rows<64>(a, s);
         return wgrad_rows<32>(a, s);
     }
-    if (ks == 3 && cin == 1 && a.c1 == 0 && !a.up && xc && a.cout % 16 == 0 && a.K == 27) {
+    if (ks == 3 && cin == 1 && a.c1 == 0 && !a.up && a.cout % 16 == 0 && a.K == 27) {
         if (xc == 128) return wgrad_c1<128>(a, s);
         if (xc == 64) return wgrad_c1<64>(a, s);
         return wgrad_c1<32>(a, s);
@@ -1680,9 +1721,7 @@ hipError_t nn_conv_wgrad(const ConvWgrad& a, int ks, hipStream_t s)
         else hipLaunchKernelGGL((k_wgrad_1x1_out1<32>), g, dim3(kSumBlock), 0, s, a, nvox);
         return hipGetLastError();
     }
-    auto lg2 = [](int n) { int l = 0; while ((1 << l) < n) ++l; return (1 << l) == n ? l : -1; };
-    const int lw = lg2(a.W), lh = lg2(a.H);
-    if (ks == 3 && lw >= 3 && lh >= 0 && (a.W * a.H) % 32 == 0 && a.cout % 16 == 0 &&
+    if (ks == 3 && pow2 && a.cout % 16 == 0 &&
         (!a.up || (a.W % 2 == 0 && a.H % 2 == 0))) {
         constexpr int NK = 2;
         const int tiles = (a.cout / 16) * (((a.K + 15) / 16 + NK - 1) / NK);

@@ -1,4 +1,4 @@
-"""The convolution kernels at the edges of their dispatch: each channel count and
+"""The convolution kernels (forward, input and weight gradient) at the edges of their dispatch: each channel count and
 channel-tile split of the whole-halo and of the plane-by-plane kernel, blocks
 that end inside a tile in x, y and z, concatenated and upsampled inputs, channel
 counts left to the general kernel, and outputs whose channels or alignment forbid
@@ -32,6 +32,10 @@ CASES = [
     # plane by plane: one, two and four channel tiles per workgroup
     (30, 33, 17, 128, 0, 64, 3, 0), (15, 33, 17, 96, 0, 64, 3, 0), (7, 6, 17, 96, 0, 128, 3, 0),
     (3, 5, 19, 32, 64, 16, 3, 0), (10, 6, 18, 64, 0, 32, 3, 1), (1, 1, 1, 32, 0, 16, 3, 0),
+    # weight gradient: rows of each chunk length, ended inside a chunk, one row of
+    # one voxel past a chunk, one input channel, rows of 16 and of 8 voxels
+    (2, 3, 65, 16, 0, 16, 3, 0), (2, 3, 127, 8, 8, 16, 3, 0), (3, 2, 129, 16, 0, 32, 3, 0), (4, 4, 62, 16, 16, 16, 3, 1),
+    (2, 3, 33, 1, 0, 16, 3, 0), (3, 2, 100, 1, 0, 32, 3, 0), (2, 4, 16, 16, 0, 16, 3, 0), (2, 4, 8, 16, 0, 16, 3, 0),
     # the general kernels
     (7, 6, 5, 40, 0, 16, 3, 0), (5, 6, 7, 56, 0, 24, 3, 0), (4, 5, 6, 72, 0, 16, 3, 0),
 ]
