@@ -174,6 +174,12 @@ ltm_tiling default_tiling(const ltm_grid& g, const ltm_camera& c, int dir)
         const uint64_t target = R <= 4 ? 1024 : 4096;    // rays per group
         t.splits = 1;
         while (t.splits < items && items / t.splits * R > target) t.splits *= 2;
+        // a detector of few groups leaves compute units idle: smaller groups, whose
+        // rays the lanes share in pieces (32^3 grid, 64^2 pixels of one
+        // ray: 22 -> 11 us; 40^3, 60^2 of 15 rays: 189 -> 34 us)
+        const uint64_t across = pl ? (c.mla_nu + t.tile_u - 1) / t.tile_u : (c.det_nu + 15) / 16;
+        const uint64_t down = pl ? (c.mla_nv + t.tile_v - 1) / t.tile_v : (c.det_nv + 15) / 16;
+        while (across * down * t.splits < 256 && items / t.splits >= 32) t.splits *= 2;
     } else if (pl && R <= 4 && oblique(c)) {
         // an optical axis oblique to the grid: bundles cross the slabs
         // diagonally, so smaller tiles and thinner slabs keep the bricks in
@@ -355,11 +361,14 @@ void bundle_geometry(const ltm_grid& g, const ltm_camera& c, CamDev& d)
             for (int r = 1; r <= R; ++r) {
                 if (r < (int)c.rays_u ? c.rays_u % r != 0 : r % c.rays_u != 0) continue;
                 const int rays = sh[0] * sh[1] * r;
-                if (rays < 32 || rays > kSharedRays) continue;
+                if (rays < 16 || rays > kSharedRays) continue;
                 const int across = std::min(r, (int)c.rays_u) - 1, rows = r / (int)c.rays_u - 1;
                 const double step = window(spread(sh[0] - 1, 2.0 * across / c.rays_u),
                                            spread(sh[1] - 1, 2.0 * std::max(rows, 0) / c.rays_v));
-                const double cost = step * (1.0 + 60.0 / rays);
+                // at least one unit per SIMD, or the others wait for the longest one
+                const double units = std::ceil((double)c.det_nu / sh[0]) * std::ceil((double)c.det_nv / sh[1]) *
+                                     std::ceil((double)R / r);
+                const double cost = step * (rays + 60.0) * std::max(units, 1024.0);
                 if (step == 0.0 || (best > 0.0 && cost >= best)) continue;
                 best = cost;
                 d.ub_u = sh[0];
@@ -402,6 +411,13 @@ void bundle_geometry(const ltm_grid& g, const ltm_camera& c, CamDev& d)
     }
     const uint64_t units = (uint64_t)d.nb_u * d.nb_v * ((R + d.ub_r - 1) / d.ub_r);
     d.n_units = units < (1ull << 20) ? (int)units : 0;
+    // too few units for a wave each: their passes of 16 cells go to four waves (with
+    // blocks of 16 rays, 32^3 grid and 64^2 pixels of one ray: 31 -> 13 us)
+    if (units <= 512) d.ub_shared = 1;
+    // a hexagonal lenslet's unit is a thousand pixels' work, so few of them run longer
+    // than the ray-by-ray sweep (units: 72 156 against 63 us, 168 135 against 113, 360
+    // 165 against 161, 572 221 against 554)
+    if (c.kind == LTM_PLENOPTIC_HEX && units < 256) d.n_units = 0;
 }
 
 // Tiling-dependent fields.
