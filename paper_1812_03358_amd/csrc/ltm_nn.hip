@@ -6,7 +6,8 @@
 // 3x3x3, offsets -1..1, zero padding), packed to BF16 for the MFMA kernels.
 //
 // Convolution = implicit GEMM on v_mfma_f32_16x16x32_bf16 (FP32 accumulate):
-// rows are output voxels, columns output channels, K runs over (tap, ci).
+// K runs over (tap, ci).  The staged 3x3x3 kernels take the weights as the first
+// operand (rows are output channels, columns voxels), the general ones the voxels.
 // Operand lane layout of the 16x16x32 instruction: lane l supplies
 // A[l % 16][8 (l / 16) + j] and B[8 (l / 16) + j][l % 16], j = 0..7, and
 // holds D[4 (l / 16) + i][l % 16], i = 0..3.
@@ -1702,13 +1703,18 @@ hipError_t nn_conv_wgrad(const ConvWgrad& a, int ks, hipStream_t s)
     int xc = 32;
     for (int c : {64, 128})
         if ((a.W + c - 1) / c * c <= (a.W + xc - 1) / xc * xc) xc = c;
-    if (ks == 3 && (a.W >= 16 || !pow2) && cin % 16 == 0 && a.c0 % 8 == 0 && a.cout % 16 == 0 && a.K == 27 * cin &&
+    // (rows of no whole chunk may come from buffers that the gathering kernels accept,
+    // aligned to an element only)
+    const bool whole = a.W % 32 == 0;
+    const bool aligned = ((reinterpret_cast<uintptr_t>(a.in0) | reinterpret_cast<uintptr_t>(a.in1) |
+                           reinterpret_cast<uintptr_t>(a.dy)) & 15) == 0;
+    if (ks == 3 && (whole || ((a.W >= 16 || !pow2) && aligned)) && cin % 16 == 0 && a.c0 % 8 == 0 && a.cout % 16 == 0 && a.K == 27 * cin &&
         (!a.up || (a.W % 2 == 0 && a.H % 2 == 0 && a.D % 2 == 0))) {
         if (xc == 128) return wgrad_rows<128>(a, s);
         if (xc == 64) return wgrad_rows<64>(a, s);
         return wgrad_rows<32>(a, s);
     }
-    if (ks == 3 && cin == 1 && a.c1 == 0 && !a.up && a.cout % 16 == 0 && a.K == 27) {
+    if (ks == 3 && cin == 1 && a.c1 == 0 && !a.up && (whole || aligned) && a.cout % 16 == 0 && a.K == 27) {
         if (xc == 128) return wgrad_c1<128>(a, s);
         if (xc == 64) return wgrad_c1<64>(a, s);
         return wgrad_c1<32>(a, s);

@@ -80,3 +80,20 @@ def test_conv_store_forms(nn, cin, cout, split, shift):
             err = np.abs(got[shift:shift + n].reshape(-1, c) - part)
             # one BF16 rounding (2^-9 of the value) and FP32 sums of values of order 1
             assert (err <= (0 if f32 else 2.0 ** -8) * np.abs(part) + 2e-5).all()
+
+
+@pytest.mark.parametrize("W,cin", [(33, 16), (16, 32), (33, 1)])
+def test_wgrad_of_element_aligned_buffers(nn, W, cin):
+    """Buffers aligned to an element only take the gathering kernels."""
+    lib = nn._lib()
+    D, H, cout = 2, 3, 16
+    g = torch.Generator().manual_seed(W + cin)
+    x = torch.randn(D * H * W * cin + 3, generator=g).bfloat16().view(torch.int16).cuda()
+    dy = torch.randn(D * H * W * cout + 3, generator=g).bfloat16().view(torch.int16).cuda()
+    desc = nn.conv_desc(3, D, H, W, cin, 0, cout, 0, relu=0, out_f32=1)
+    got = []
+    for a, b in ((x[3:], dy[3:]), (x[3:].clone(), dy[3:].clone())):
+        dw = torch.zeros(cout, 27 * cin, device="cuda")
+        assert lib.ltm_nn_conv3d_wgrad(ctypes.byref(desc), nn._p(a), None, nn._p(b), nn._p(dw), None) == 0
+        got.append(dw.cpu().numpy())
+    assert T.rel(got[0], got[1]) < 1e-5
