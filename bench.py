@@ -168,7 +168,8 @@ def roofline_of(valid, fwd_ms, adj_ms):
     achieved = FLOP_PER_SAMPLE[dominant] * valid / (dom_ms * 1e-3) / 1e12
     roof = {"bound": "alu", "achieved": round(achieved, 3), "peak": round(PEAK_FP32_TFLOPS, 2),
             "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": None,
-            "kernel": "k_march<true> (adjoint)" if dominant == "backproject" else "k_march<false> (forward)",
+            "kernel": "k_bundle or k_march<true> (adjoint)" if dominant == "backproject"
+            else "k_march<false> (forward)",
             "ms_per_launch": round(dom_ms, 4),
             "frac_of_non_packed_fp32": round(achieved / PEAK_FP32_NON_PACKED_TFLOPS, 4)}
     gather = {d: round(valid / (ms * 1e-3) * GATHER_BYTES_PER_SAMPLE / 1e9 / HBM_PEAK_GBS, 4)
@@ -407,7 +408,7 @@ def run_batched(args):
                       {"valid_samples_per_direction": valid, "nominal_samples_per_direction": nominal,
                        "frames": len(frames), "cameras_per_frame": 4})
     roof, gather = roofline_of(valid, fwd_ms, adj_ms)
-    roof["kernel"] = "k_batch<true> (adjoint sweep)" if adj_ms >= fwd_ms else "k_batch<false> (forward sweep)"
+    roof["kernel"] = "k_batch (adjoint sweep)" if adj_ms >= fwd_ms else "k_batch (forward sweep)"
     roof["traffic"] = counter_traffic_batch(adj_ms >= fwd_ms)
     out["roofline"] = roof
     out["gather_equivalent_hbm_frac_not_a_roofline"] = gather
