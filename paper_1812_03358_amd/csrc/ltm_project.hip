@@ -489,25 +489,40 @@ __device__ __forceinline__ March march_of(const Ray& r)
     return m;
 }
 
+// Sum of a ray's samples m0 .. m1 - 1 from a staged brick.  VALU issue bounds it,
+// so whole groups of 8 samples are unrolled without the loop's count and compare
+// and the cell's address comes from the float chain as it is: project of 128^3 to
+// 1024^2 pixels 334 -> 295 us (two samples per trip 308).
 __device__ __forceinline__ double gather_lds(const March& mr, int m0, int m1, const BrickRec& b,
                                              const float* brick, const Bounds& bd)
 {
-    const float dx = (float)b.dim[0], dxy = (float)(b.dim[0] * b.dim[1]);
+    typedef const __attribute__((address_space(3))) float* LdsPtr;
+    // the cell's LDS address in bytes, as a float: whole multiples of 4, exact to 2^26
+    const unsigned at = (unsigned)(uintptr_t)(LdsPtr)brick;
+    const float dx = 4.0f * (float)b.dim[0], dxy = 4.0f * (float)(b.dim[0] * b.dim[1]);
     const int sx = b.dim[0], sxy = b.dim[0] * b.dim[1];
-    const float maxi = (float)(b.dim[0] * b.dim[1] * b.dim[2] - 1 - (1 + sx + sxy));
+    const float lo = (float)at, hi = (float)(at + 4u * (unsigned)(b.dim[0] * b.dim[1] * b.dim[2] - 1 - (1 + sx + sxy)));
+    const float base = lo - 4.0f * b.base;
+    auto sample = [&](float fm) {
+        const Cell s = cell_of_padded(fmaf(fm, mr.st[0], mr.qs[0]), fmaf(fm, mr.st[1], mr.qs[1]),
+                                      fmaf(fm, mr.st[2], mr.qs[2]));
+        const float fi = fmaf(s.i[2], dxy, fmaf(s.i[1], dx, fmaf(s.i[0], 4.0f, base)));
+        LdsPtr p = (LdsPtr)(uintptr_t)(unsigned)(int)clampf(fi, lo, hi);
+        return tri(p[0], p[1], p[sx], p[sx + 1], p[sxy], p[sxy + 1], p[sxy + sx], p[sxy + sx + 1], s);
+    };
     double acc = 0.0;
     // samples are summed in FP32 groups of up to 8, each group added in FP64
-    for (int g0 = m0; g0 < m1; g0 += 8) {
-        const float fend = (float)min(g0 + 8, m1);
+    int g0 = m0;
+    for (; g0 + 8 <= m1; g0 += 8) {
+        float part = 0.0f, fm = (float)g0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j, fm += 1.0f) part += sample(fm);
+        acc += (double)part;
+    }
+    if (g0 < m1) {
+        const float fend = (float)m1;
         float part = 0.0f;
-        for (float fm = (float)g0; fm < fend; fm += 1.0f) {
-            const Cell s = cell_of_padded(fmaf(fm, mr.st[0], mr.qs[0]), fmaf(fm, mr.st[1], mr.qs[1]),
-                                   fmaf(fm, mr.st[2], mr.qs[2]));
-            const float fi = fmaf(s.i[2], dxy, fmaf(s.i[1], dx, s.i[0])) - b.base;
-            const int i0 = (int)clampf(fi, 0.0f, maxi);
-            const float* p = brick + i0;
-            part += tri(p[0], p[1], p[sx], p[sx + 1], p[sxy], p[sxy + 1], p[sxy + sx], p[sxy + sx + 1], s);
-        }
+        for (float fm = (float)g0; fm < fend; fm += 1.0f) part += sample(fm);
         acc += (double)part;
     }
     return acc;
