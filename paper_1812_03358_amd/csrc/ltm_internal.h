@@ -116,7 +116,6 @@ struct Accumulator {
 };
 constexpr int kUnitRays = 128;    // rays a wave of the bundled adjoint holds at once
 constexpr int kSharedRays = 576;  // rays a workgroup of it holds at once (4 workgroups share a CU's LDS)
-constexpr int kPartRegs = 10;     // FP64 words per lane of a wave's partial sums (windows of up to 5 x 4)
 constexpr int kTileBits = 20;   // work item = (batch camera << 20) | tile
 
 struct CamHost {

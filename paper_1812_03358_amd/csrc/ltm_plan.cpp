@@ -345,9 +345,9 @@ void bundle_geometry(const ltm_grid& g, const ltm_camera& c, CamDev& d)
         for (int k = 0; k < 2; ++k)
             w[k] = drift[k] + (ws * (std::fabs(es[t[k]]) + drift[k] * std::fabs(es[d.dom])) +
                                wt * (std::fabs(et[t[k]]) + drift[k] * std::fabs(et[d.dom]))) / g.pitch_mm;
-        if (w[1] <= 0.95) return w[0] <= 0.95 ? 40.0 : (w[0] <= 1.95 ? 49.0 : (w[0] <= 2.95 ? 58.0 : 0.0));
+        if (w[1] <= 0.95) return w[0] <= 0.95 ? 47.0 : (w[0] <= 1.95 ? 58.0 : (w[0] <= 2.95 ? 69.0 : 0.0));
         if (w[1] > 1.95) return 0.0;
-        return w[0] <= 1.95 ? 62.0 : (w[0] <= 2.95 ? 73.0 : 0.0);
+        return w[0] <= 1.95 ? 71.0 : (w[0] <= 2.95 ? 84.0 : 0.0);
     };
     d.ub_shared = d.ub_rfast = 0;
     const int R = (int)(c.rays_u * c.rays_v);

@@ -767,18 +767,18 @@ __device__ __forceinline__ void scatter_global(const March& mr, int m0, int m1, 
 // along grid axis dom (a lane's samples have their dom coordinate in one cell
 // [k, k + 1)) times 4 rays, which walk the unit's rays 4 at a time.  A lane sums
 // its samples into a private WA x WB window of voxels of planes k and k + 1 held
-// in registers, and only when the unit is done are the four rays' windows added
-// and sent to the FP64 accumulator: about 0.08 atomics per sample instead of 4-8
-// LDS atomics per cell step of every ray, and no per-sample cell search, bricks
-// or barriers.
+// in FP64 registers, and only when the unit is done are the four rays' windows
+// added and sent to the FP64 accumulator: about 0.08 atomics per sample instead of
+// 4-8 LDS atomics per cell step of every ray, and no per-sample cell search,
+// bricks or barriers.
 //
 // Against the ray-by-ray adjoint (scatter_lds_window) of the same cameras, ms:
-// plenoptic 1024^2 on 128^3 0.81 -> 0.50 head-on, 1.48 -> 0.72 at 30 degrees,
-// 3.73 -> 0.80 at 45; hexagonal 2048^2 on 100^3 4.78 -> 1.92, 7.32 -> 2.94 at 20
-// degrees; single-lens 461 x 400 with 64 samples per pixel 8.08 -> 3.21 at 30
-// degrees, 5.27 -> 2.51 head-on.  VALU issue bounds it: 61 instructions per
-// sample and lane head-on (86 ray by ray, at 60% of the issue rate for the
-// waits on LDS atomics), 40 of them a sample's step in the 3 x 3 window.
+// plenoptic 1024^2 on 128^3 0.80 -> 0.59 head-on, 1.46 -> 0.84 at 30 degrees,
+// 3.79 -> 1.02 at 45; hexagonal 2048^2 on 100^3 4.77 -> 2.26, 7.33 -> 3.48 at 20
+// degrees; single-lens 461 x 400 with 64 samples per pixel 8.07 -> 3.98 at 30
+// degrees, 5.32 -> 3.21 head-on.  The FP64 sums are what keeps it from more: with
+// FP32 sums over some 32 samples of the unit's rays it took 0.47, 0.70, 0.78, 1.88,
+// 2.87, 3.13 and 2.52, but different rays have always met in FP64.
 struct BundleRay {
     // position of sample m: (a0 + m da, b0 + m db, c0 + m dc) along the two
     // transverse axes and dom; inv = 1 / (S dc); v: the weighted pixel value
@@ -838,18 +838,40 @@ __device__ __forceinline__ float wave_min_dpp(float v)
 }
 
 // x + (x of the other half wave) in lanes 0-31, the same of y in lanes 32-63.
-__device__ __forceinline__ float fold32(float x, float y)
+__device__ __forceinline__ double fold32(double x, double y)
 {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
 }
 
 // Row 0: x of rows 0 and 1, row 1: y of rows 0 and 1, row 2: x of rows 2 and
 // 3, row 3: y of rows 2 and 3.
-__device__ __forceinline__ float fold16(float x, float y)
+__device__ __forceinline__ double fold16(double x, double y)
 {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+// The camera's constants, read anew (scalar loads) by the stage that asks for them.
+// As values known from the kernel's start on, what derives from them (floats of the
+// sizes, reciprocals, edges) is computed there once and then waits in scratch memory
+// while the windows fill the registers (248 bytes a lane instead of 100: the head-on
+// 128^3 camera 638 us against 591, with an image of zeros 55 us against 33).
+typedef const __attribute__((address_space(4))) CamDev* CamPtr;
+
+__device__ __forceinline__ const CamDev& fresh(CamPtr cam)
+{
+    asm volatile("" : "+s"(cam));
+    return *(const CamDev*)cam;
+}
+
+__device__ __forceinline__ int fresh_lane()
+{
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    return lane;
 }
 
 // What is known of some rays of a unit: the cells [k0, k1) along dom that hold
@@ -891,31 +913,25 @@ __device__ __forceinline__ void window_weights(float q, float w1, float (&w)[W])
     w[W - 1] = clampf(q - (w1 + (float)(W - 3)), 0.0f, 1.0f);
 }
 
-// Rays in LDS: (a0, da, b0, db) and (c0, dc, inv, v) of each; the wave's FP64
-// sums (64 kPartRegs words); and which of the rays' passes of 16 cells this wave
-// takes: first, first + stride, ...
+// Rays in LDS: (a0, da, b0, db) and (c0, dc, inv, v) of each; and which of the
+// rays' passes of 16 cells this wave takes: first, first + stride, ...
 struct UnitRays {
     float4* ab;
     float4* cv;
-    double* part;
     int first, stride;
 };
 
-// Steps whose FP32 sums are kept in one register (the rounding of a sum of n
-// terms spreads as sqrt(n / 3) of one); all blocks' and units' sums meet in FP64.
-constexpr int kBlockSteps = 32;
-
 // Scatter rays [i0, i1) of P, 16 cells at a time.  What bounds it is VALU
-// issue: a step (one sample in each lane) is 39 instructions at WA = WB = 3,
-// of which 18 are the window's FMAs, and finding a ray's sample range in a
-// cell is about 10 per ray and cell.
+// issue: a step (one sample in each lane) is 47 instructions at WA = WB = 3,
+// of which 18 are the window's FP64 FMAs and 10 lead to their operands, and
+// finding a ray's sample range in a cell is about 10 per ray and cell.
 template <int WA, int WB>
-__device__ __forceinline__ void bundle_cells(const CamDev& c, const BundleCells& s, const UnitRays& P, int i0,
-                                             int i1, double* __restrict__ xacc)
+__device__ __forceinline__ void bundle_cells(CamPtr cam, const BundleCells& s, const UnitRays& P, int i0, int i1,
+                                             double* __restrict__ xacc)
 {
-    const int lane = threadIdx.x & 63;
-    const int p = lane & 15, j = lane >> 4;
-    const float S = (float)c.S;
+    const int p = threadIdx.x & 15, j = (threadIdx.x & 63) >> 4;
+    const float S = (float)fresh(cam).S;
+    const bool falls = fresh(cam).dom_sign < 0;
     for (int kg = s.k0 + 16 * P.first; kg < s.k1; kg += 16 * P.stride) {
         // a pass of n <= 8 cells gives each cell 16 / 2^ceil(log2 n) lanes,
         // which share its samples (rays that only graze a corner of the grid
@@ -929,7 +945,7 @@ __device__ __forceinline__ void bundle_cells(const CamDev& c, const BundleCells&
         float ea = k == s.k0 ? -kFarPlane : kf;
         float eb = k == s.k1 - 1 ? kFarPlane : kf + 1.0f;
         if (k >= s.k1) ea = eb = kFarPlane;
-        if (c.dom_sign < 0) {
+        if (falls) {
             const float t = ea;
             ea = eb;
             eb = t;
@@ -937,90 +953,78 @@ __device__ __forceinline__ void bundle_cells(const CamDev& c, const BundleCells&
         float span;
         const float a0 = cell_window(s, k, 0, span), b0 = cell_window(s, k, 1, span);
         const float a1 = a0 + 1.0f, b1 = b0 + 1.0f;
+        // sums of v wa wb, and of the same times the dom fraction, over the lane's
+        // samples: the rays of a unit meet in FP64
+        double T[WA][WB], H[WA][WB];
+#pragma unroll
+        for (int x = 0; x < WA; ++x)
+#pragma unroll
+            for (int y = 0; y < WB; ++y) T[x][y] = H[x][y] = 0.0;
+        auto walk = [&](auto split) {
+            for (int i = i0; i < i1; i += 4) {
+                const float4 q = P.ab[i + j], r = P.cv[i + j];
+                float fm = plane_edge(r.x, r.z, ea, S);
+                float fe = plane_edge(r.x, r.z, eb, S);
+                if constexpr (decltype(split)::value) {
+                    const float len = fe - fm;
+                    fe = fm + floorf(len * (from + share));
+                    fm += floorf(len * from);
+                }
+                if (__ballot(fm < fe)) do {
+                    const float v = r.w * clampf(fe - fm, 0.0f, 1.0f);   // 0 past the cell's samples
+                    const double fc = (double)clampf(fmaf(fm, r.y, r.x) - kf, 0.0f, 1.0f);
+                    float wa[WA], wb[WB];
+                    window_weights<WA>(fmaf(fm, q.y, q.x), a1, wa);
+                    window_weights<WB>(fmaf(fm, q.w, q.z), b1, wb);
+                    double va[WA];
+#pragma unroll
+                    for (int x = 0; x < WA; ++x) va[x] = (double)(wa[x] * v);
+#pragma unroll
+                    for (int y = 0; y < WB; ++y) {
+                        const double w = (double)wb[y], wh = w * fc;
+#pragma unroll
+                        for (int x = 0; x < WA; ++x) {
+                            T[x][y] = fma(va[x], w, T[x][y]);
+                            H[x][y] = fma(va[x], wh, H[x][y]);
+                        }
+                    }
+                    fm += 1.0f;
+                } while (__ballot(fm < fe));
+            }
+        };
+        if (lg < 4)
+            walk(std::true_type{});
+        else
+            walk(std::false_type{});
+        // add the four rays' windows: entry e = x WB + y of plane k (lanes
+        // 0-31) and k + 1 (lanes 32-63), then two entries per register, one in
+        // the even and one in the odd rows of 16 lanes
         constexpr int kEntries = WA * WB, kRegs = (kEntries + 1) / 2;
         double total[kRegs];
-        int i = i0;
-        // blocks of rays of some kBlockSteps steps: FP32 sums within a block, FP64
-        // across blocks (in the wave's LDS words) and units
-        for (bool first = true;; first = false) {
-            float T[WA][WB], H[WA][WB];   // sums of v wa wb, and of the same times the dom fraction
 #pragma unroll
-            for (int x = 0; x < WA; ++x)
+        for (int e = 0; e < kRegs; ++e) {
+            double half[2] = {0.0, 0.0};
 #pragma unroll
-                for (int y = 0; y < WB; ++y) T[x][y] = H[x][y] = 0.0f;
-            auto walk = [&](auto split) {
-                int steps = 0;
-                do {
-                    const float4 q = P.ab[i + j], r = P.cv[i + j];
-                    i += 4;
-                    float fm = plane_edge(r.x, r.z, ea, S);
-                    float fe = plane_edge(r.x, r.z, eb, S);
-                    if constexpr (decltype(split)::value) {
-                        const float len = fe - fm;
-                        fe = fm + floorf(len * (from + share));
-                        fm += floorf(len * from);
-                    }
-                    if (__ballot(fm < fe)) {
-                        do {
-                            const float v = r.w * clampf(fe - fm, 0.0f, 1.0f);   // 0 past the cell's samples
-                            const float fc = clampf(fmaf(fm, r.y, r.x) - kf, 0.0f, 1.0f);
-                            float wa[WA], wb[WB];
-                            window_weights<WA>(fmaf(fm, q.y, q.x), a1, wa);
-                            window_weights<WB>(fmaf(fm, q.w, q.z), b1, wb);
-#pragma unroll
-                            for (int x = 0; x < WA; ++x) wa[x] *= v;
-#pragma unroll
-                            for (int y = 0; y < WB; ++y) {
-                                const float wh = wb[y] * fc;
-#pragma unroll
-                                for (int x = 0; x < WA; ++x) {
-                                    T[x][y] = fmaf(wa[x], wb[y], T[x][y]);
-                                    H[x][y] = fmaf(wa[x], wh, H[x][y]);
-                                }
-                            }
-                            fm += 1.0f;
-                            ++steps;
-                        } while (__ballot(fm < fe));
-                    }
-                } while (i < i1 && steps < kBlockSteps);
-            };
-            if (lg < 4)
-                walk(std::true_type{});
-            else
-                walk(std::false_type{});
-            // add the four rays' windows: entry e = x WB + y of plane k (lanes
-            // 0-31) and k + 1 (lanes 32-63), then two entries per register, one in
-            // the even and one in the odd rows of 16 lanes
-            float half[2 * kRegs];
-#pragma unroll
-            for (int e = 0; e < 2 * kRegs; ++e) {
-                half[e] = 0.0f;
-                if (e < kEntries) {
-                    const float h = H[e / WB][e % WB];
-                    half[e] = fold32(T[e / WB][e % WB] - h, h);
+            for (int o = 0; o < 2; ++o)
+                if (2 * e + o < kEntries) {
+                    const int x = (2 * e + o) / WB, y = (2 * e + o) % WB;
+                    half[o] = fold32(T[x][y] - H[x][y], H[x][y]);
                 }
-            }
-            double* part = P.part + lane;
-#pragma unroll
-            for (int e = 0; e < kRegs; ++e) {
-                total[e] = (double)fold16(half[2 * e], half[2 * e + 1]);
-                if (!first) total[e] += part[64 * e];
-            }
-            if (i >= i1) break;
-#pragma unroll
-            for (int e = 0; e < kRegs; ++e) part[64 * e] = total[e];
+            total[e] = fold16(half[0], half[1]);
         }
         // the window's voxels, clamped to the grid: the layer outside it is a
         // copy of its outermost voxels
+        const CamDev& c = fresh(cam);
+        const int row = fresh_lane() >> 4;
         const bool dx = c.dom == 0, dy = c.dom == 1;
         const int na = dx ? c.n[2] : c.n[0], nb = dy ? c.n[2] : c.n[1];
         const int nc = dx ? c.n[0] : (dy ? c.n[1] : c.n[2]);
-        const int gc = min(max(k + (j >> 1), 0), nc - 1);
+        const int gc = min(max(k + (row >> 1), 0), nc - 1);
         const int ga0 = (int)a0, gb0 = (int)b0;
 #pragma unroll
         for (int e = 0; e < kRegs; ++e) {
             if (total[e] == 0.0) continue;
-            const bool odd = j & 1;
+            const bool odd = row & 1;
             const int ga = min(max(ga0 + (odd ? (2 * e + 1) / WB : 2 * e / WB), 0), na - 1);
             const int gb = min(max(gb0 + (odd ? (2 * e + 1) % WB : 2 * e % WB), 0), nb - 1);
             const int gx = dx ? gc : ga, gy = dy ? gc : gb, gz = dx ? ga : (dy ? gb : gc);
@@ -1033,10 +1037,10 @@ __device__ __forceinline__ void bundle_cells(const CamDev& c, const BundleCells&
 // no window holds them, if one turns away from dom, or if a value is not finite
 // (its products with a window's zero weights would reach voxels that it does
 // not touch) or near the end of the FP32 range.
-__device__ __forceinline__ bool bundle_scatter(const CamDev& c, const UnitRays& P, int i0, int i1,
-                                               double* __restrict__ xacc)
+__device__ __forceinline__ bool bundle_scatter(CamPtr cam, const UnitRays& P, int i0, int i1, double* __restrict__ xacc)
 {
-    const int lane = threadIdx.x & 63;
+    const CamDev& c = fresh(cam);
+    const int lane = fresh_lane();
     const int nc = c.dom == 0 ? c.n[0] : (c.dom == 1 ? c.n[1] : c.n[2]);
     const float last = (float)(c.S - 1);
     float qlo = FLT_MAX, qhi = FLT_MAX;   // first and (negated) last dom coordinates
@@ -1107,22 +1111,24 @@ __device__ __forceinline__ bool bundle_scatter(const CamDev& c, const UnitRays& 
     // padding follows a whole list, and a part's length is a multiple of 4
     const bool na4 = __ballot(na > 4.0f) != 0, nb3 = __ballot(nb > 3.0f) != 0;
     if (na4 && nb3)
-        bundle_cells<5, 4>(c, s, P, i0, i1, xacc);
+        bundle_cells<5, 4>(cam, s, P, i0, i1, xacc);
     else if (nb3)
-        bundle_cells<4, 4>(c, s, P, i0, i1, xacc);
+        bundle_cells<4, 4>(cam, s, P, i0, i1, xacc);
     else if (na4)
-        bundle_cells<5, 3>(c, s, P, i0, i1, xacc);
+        bundle_cells<5, 3>(cam, s, P, i0, i1, xacc);
     else if (__ballot(na > 3.0f))
-        bundle_cells<4, 3>(c, s, P, i0, i1, xacc);
+        bundle_cells<4, 3>(cam, s, P, i0, i1, xacc);
     else
-        bundle_cells<3, 3>(c, s, P, i0, i1, xacc);
+        bundle_cells<3, 3>(cam, s, P, i0, i1, xacc);
     return true;
 }
 
 // Samples of up to 4 rays added to the accumulator one by one, 16 lanes a ray.
-__device__ __forceinline__ void scatter_samples(const CamDev& c, const Bounds& bd, const UnitRays& P, int i0,
-                                                int i1, double* __restrict__ xacc)
+__device__ __forceinline__ void scatter_samples(CamPtr cam, const UnitRays& P, int i0, int i1,
+                                                double* __restrict__ xacc)
 {
+    const CamDev& c = fresh(cam);
+    const Bounds bd = bounds_of(c.n);
     const int i = i0 + ((threadIdx.x & 63) >> 4);
     if (i >= i1) return;
     const float4 q = P.ab[i], r = P.cv[i];
@@ -1143,18 +1149,18 @@ __device__ __forceinline__ void scatter_samples(const CamDev& c, const Bounds& b
 
 // The collected rays P[0, cnt): all at once if their windows hold them,
 // otherwise in halves, down to 4 rays, whose samples then go one by one.
-__device__ __forceinline__ void bundle_flush(const CamDev& c, const Bounds& bd, const UnitRays& P, int cnt,
+__device__ __forceinline__ void bundle_flush(CamPtr cam, const UnitRays& P, int cnt,
                                              double* __restrict__ xacc)
 {
     int len = (cnt + 3) & ~3;
     for (int i = 0; i < cnt;) {
         const int end = min(i + len, cnt);
-        if (!bundle_scatter(c, P, i, end, xacc)) {
+        if (!bundle_scatter(cam, P, i, end, xacc)) {
             if (len > 4) {
                 len = ((len >> 1) + 3) & ~3;
                 continue;
             }
-            if (P.first == 0) scatter_samples(c, bd, P, i, end, xacc);
+            if (P.first == 0) scatter_samples(cam, P, i, end, xacc);
         }
         i = end;
     }
@@ -1173,100 +1179,102 @@ __device__ __forceinline__ void wave_sync()
 // of 16 cells in turn, so that many rays share one window and one set of
 // atomics; otherwise a wave has a unit, of up to kUnitRays rays, to itself.
 template <bool kShared>
-__device__ __forceinline__ void bundle_unit(const CamDev& c, int unit, const float* __restrict__ y,
+__device__ __forceinline__ void bundle_unit(CamPtr cam, int unit, const float* __restrict__ y,
                                             double* __restrict__ xacc, float4* lds, int* wsum)
 {
     constexpr int kLanes = kShared ? kThreads : 64;
     constexpr int kCap = kShared ? kSharedRays : kUnitRays;
-    if (unit >= c.n_units) return;
+    if (unit >= fresh(cam).n_units) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int id = kShared ? (int)threadIdx.x : lane;
-    const UnitRays P = {lds, lds + kCap,
-                        reinterpret_cast<double*>(lds + 2 * kCap) + (kShared ? wave * 64 * kPartRegs : 0),
-                        kShared ? wave : 0, kShared ? kThreads / 64 : 1};
-    const Bounds bd = bounds_of(c.n);
-    const int R = c.ru * c.grv, nrr = (R + c.ub_r - 1) / c.ub_r, blocks = c.nb_u * c.nb_v;
+    const UnitRays P = {lds, lds + kCap, kShared ? wave : 0, kShared ? kThreads / 64 : 1};
+    const CamDev& c0 = fresh(cam);
+    const int R = c0.ru * c0.grv, nrr = (R + c0.ub_r - 1) / c0.ub_r, blocks = c0.nb_u * c0.nb_v;
     // aperture samples or blocks vary fastest (ub_rfast)
-    const int blk = c.ub_rfast ? unit / nrr : unit % blocks;
-    const int r0 = (c.ub_rfast ? unit - blk * nrr : unit / blocks) * c.ub_r;
-    const int bv = blk / c.nb_u, bu = blk - bv * c.nb_u;
-    int iu0 = bu * c.ub_u, iv0 = bv * c.ub_v;
-    Lenslet L = {0.0f, 0.0f, c.Ag, c.Bg, c.Lg};
-    if (c.kind == LTM_PLENOPTIC) {
-        L.cu = (float)bu + 0.5f - 0.5f * (float)c.mu;
-        L.cv = (float)bv + 0.5f - 0.5f * (float)c.mv;
-    } else if (c.kind == LTM_PLENOPTIC_HEX) {
-        hex_lenslet(c, bu, bv, L);
-        iu0 = (int)rintf(fmaf(L.cu, c.ub_cu, 0.5f * (float)(c.nu - 1))) - (c.ub_u >> 1);
-        iv0 = (int)rintf(fmaf(L.cv, c.ub_cv, 0.5f * (float)(c.nv - 1))) - (c.ub_v >> 1);
-    }
-    const int npx = c.ub_u * c.ub_v, total = npx * min(c.ub_r, R - r0);
-    int cnt = 0;
-    for (int base = 0; base < total; base += kLanes) {
-        const int e = base + id;
-        const int re = e / npx, px = e - re * npx;
-        const int pv = px / c.ub_u, pu = px - pv * c.ub_u;
-        const int iu = iu0 + pu, iv = iv0 + pv;
-        bool ok = e < total && (unsigned)iu < (unsigned)c.nu && (unsigned)iv < (unsigned)c.nv;
-        BundleRay b;
-        if (ok) {
-            const float v = y[c.y_off + (size_t)iv * c.nu + iu];
-            const int rr = r0 + re, rv = rr / c.ru, ru = rr - rv * c.ru;
-            float gs, gt;
-            Ray r;
-            ok = v != 0.0f && aperture_sample(c, ru, rv, gs, gt) &&
-                 trace_ray(c, (float)iu + 0.5f - 0.5f * (float)c.nu, (float)iv + 0.5f - 0.5f * (float)c.nv, L,
-                           gs, gt, r);
-            if (ok) b = bundle_ray(c, r, v);
+    const int blk = c0.ub_rfast ? unit / nrr : unit % blocks;
+    const int r0 = (c0.ub_rfast ? unit - blk * nrr : unit / blocks) * c0.ub_r;
+    const int total = c0.ub_u * c0.ub_v * min(c0.ub_r, R - r0);
+    for (int base = 0; base < total;) {
+        const CamDev& c = fresh(cam);
+        const int npx = c.ub_u * c.ub_v;
+        const int bv = blk / c.nb_u, bu = blk - bv * c.nb_u;
+        int iu0 = bu * c.ub_u, iv0 = bv * c.ub_v;
+        Lenslet L = {0.0f, 0.0f, c.Ag, c.Bg, c.Lg};
+        if (c.kind == LTM_PLENOPTIC) {
+            L.cu = (float)bu + 0.5f - 0.5f * (float)c.mu;
+            L.cv = (float)bv + 0.5f - 0.5f * (float)c.mv;
+        } else if (c.kind == LTM_PLENOPTIC_HEX) {
+            hex_lenslet(c, bu, bv, L);
+            iu0 = (int)rintf(fmaf(L.cu, c.ub_cu, 0.5f * (float)(c.nu - 1))) - (c.ub_u >> 1);
+            iv0 = (int)rintf(fmaf(L.cv, c.ub_cv, 0.5f * (float)(c.nv - 1))) - (c.ub_v >> 1);
         }
-        const unsigned long long bal = __ballot(ok);
-        int at = cnt + __popcll(bal & ((1ull << lane) - 1ull)), all = __popcll(bal);
-        if constexpr (kShared) {
-            __syncthreads();   // the previous pass's counts are read
-            if (lane == 0) wsum[wave] = all;
-            __syncthreads();
-            all = 0;
-#pragma unroll
-            for (int w = 0; w < kThreads / 64; ++w) {
-                at += w < wave ? wsum[w] : 0;
-                all += wsum[w];
+        int cnt = 0;
+        for (; base < total && cnt <= kCap - kLanes; base += kLanes) {
+            const int e = base + id;
+            const int re = e / npx, px = e - re * npx;
+            const int pv = px / c.ub_u, pu = px - pv * c.ub_u;
+            const int iu = iu0 + pu, iv = iv0 + pv;
+            bool ok = e < total && (unsigned)iu < (unsigned)c.nu && (unsigned)iv < (unsigned)c.nv;
+            BundleRay b;
+            if (ok) {
+                const float v = y[c.y_off + (size_t)iv * c.nu + iu];
+                const int rr = r0 + re, rv = rr / c.ru, ru = rr - rv * c.ru;
+                float gs, gt;
+                Ray r;
+                ok = v != 0.0f && aperture_sample(c, ru, rv, gs, gt) &&
+                     trace_ray(c, (float)iu + 0.5f - 0.5f * (float)c.nu, (float)iv + 0.5f - 0.5f * (float)c.nv, L,
+                               gs, gt, r);
+                if (ok) b = bundle_ray(c, r, v);
             }
+            const unsigned long long bal = __ballot(ok);
+            int at = cnt + __popcll(bal & ((1ull << lane) - 1ull)), all = __popcll(bal);
+            if constexpr (kShared) {
+                __syncthreads();   // the previous pass's counts are read
+                if (lane == 0) wsum[wave] = all;
+                __syncthreads();
+                all = 0;
+#pragma unroll
+                for (int w = 0; w < kThreads / 64; ++w) {
+                    at += w < wave ? wsum[w] : 0;
+                    all += wsum[w];
+                }
+            }
+            if (ok) {
+                P.ab[at] = float4{b.a0, b.da, b.b0, b.db};
+                P.cv[at] = float4{b.c0, b.dc, b.inv, b.v};
+            }
+            cnt += all;
         }
-        if (ok) {
-            P.ab[at] = float4{b.a0, b.da, b.b0, b.db};
-            P.cv[at] = float4{b.c0, b.dc, b.inv, b.v};
-        }
-        cnt += all;
-        if (cnt > 0 && (cnt > kCap - kLanes || base + kLanes >= total)) {
+        if (cnt > 0) {
             if (id < 4 && cnt + id < kCap) {
                 // padding: an empty sample range (both edges are 0) and no value
                 P.ab[cnt + id] = float4{0.f, 0.f, 0.f, 0.f};
                 P.cv[cnt + id] = float4{0.f, 0.f, 0.f, 0.f};
             }
             kShared ? __syncthreads() : wave_sync();
-            bundle_flush(c, bd, P, cnt, xacc);
+            bundle_flush(cam, P, cnt, xacc);
             kShared ? __syncthreads() : wave_sync();
-            cnt = 0;
         }
     }
 }
 
 // The units of one tile: one shared by the workgroup, or one per wave.
-__device__ __forceinline__ void bundle_tile(const CamDev& c, int tile, const float* __restrict__ y,
+__device__ __forceinline__ void bundle_tile(CamPtr c, int tile, const float* __restrict__ y,
                                             double* __restrict__ xacc, float4* lds, int* wsum)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (c.ub_shared)
+    if (fresh(c).ub_shared)
         bundle_unit<true>(c, tile, y, xacc, lds, wsum);
     else
         bundle_unit<false>(c, tile * (kThreads / 64) + wave, y, xacc,
-                           lds + wave * (2 * kUnitRays + 32 * kPartRegs), wsum);
+                           lds + wave * 2 * kUnitRays, wsum);
 }
 
 template <bool kShared>
-__global__ __launch_bounds__(kThreads, 4) void k_bundle(CamDev c, const float* __restrict__ y,
+__global__ __launch_bounds__(kThreads, 4) void k_bundle(CamDev, const float* __restrict__ y,
                                                         double* __restrict__ xacc)
 {
+    const CamPtr c = (CamPtr)__builtin_amdgcn_kernarg_segment_ptr();   // the first argument, as it lies there
     extern __shared__ float4 rays[];
     __shared__ int wsum[kThreads / 64];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1274,7 +1282,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_bundle(CamDev c, const float* _
         bundle_unit<true>(c, blockIdx.x, y, xacc, rays, wsum);
     else
         bundle_unit<false>(c, (int)blockIdx.x * (kThreads / 64) + wave, y, xacc,
-                           rays + wave * (2 * kUnitRays + 32 * kPartRegs), wsum);
+                           rays + wave * 2 * kUnitRays, wsum);
 }
 
 // ---------------------------------------------------------------- A x, A^T y
@@ -1511,7 +1519,7 @@ enum class Sweep { forward, rays, bundles, mixed };
 // (every workgroup reaches the exit once the counter passes n_items).
 // Items are ordered by decreasing estimated cost.
 template <Sweep kSweep>
-__global__ __launch_bounds__(kThreads, kSweep == Sweep::bundles ? 4 : 5) void k_batch(
+__global__ __launch_bounds__(kThreads, kSweep == Sweep::bundles || kSweep == Sweep::mixed ? 4 : 5) void k_batch(
     const BatchCam* __restrict__ cams, const uint32_t* __restrict__ items, uint32_t n_items,
     unsigned int* __restrict__ counter)
 {
@@ -1532,7 +1540,7 @@ __global__ __launch_bounds__(kThreads, kSweep == Sweep::bundles ? 4 : 5) void k_
             march_tile<false>(bc.cam, tile, bc.x, bc.y, nullptr, smem, wsum);
         } else {
             if (kSweep == Sweep::bundles || (kSweep == Sweep::mixed && bc.cam.bundle)) {
-                bundle_tile(bc.cam, tile, bc.y, bc.xacc, reinterpret_cast<float4*>(smem), wsum);
+                bundle_tile((CamPtr)(uintptr_t)&bc.cam, tile, bc.y, bc.xacc, reinterpret_cast<float4*>(smem), wsum);
             } else if constexpr (kSweep != Sweep::bundles) {
                 march_tile<true>(bc.cam, tile, bc.y, nullptr, bc.xacc, smem, wsum);
             }
@@ -1692,8 +1700,7 @@ hipError_t launch_setup(const CamDev& c, int dir, hipStream_t s)
 size_t march_lds_bytes(const CamDev& c, int dir)
 {
     if (dir == LTM_ADJOINT && c.bundle)
-        return (c.ub_shared ? kSharedRays : kThreads / 64 * kUnitRays) * 2 * sizeof(float4) +
-               kThreads * kPartRegs * sizeof(double);
+        return (c.ub_shared ? kSharedRays : kThreads / 64 * kUnitRays) * 2 * sizeof(float4);
     const size_t list_bytes = ((size_t)c.items_per_split * c.ru * c.rv * 4 + 15) & ~size_t(15);
     const size_t item_bytes = ((size_t)c.items_per_split * 8 + 15) & ~size_t(15);
     const size_t brick_bytes = (size_t)c.brick_cap * ((dir == LTM_ADJOINT && !c.adj_f32) ? 8 : 4);

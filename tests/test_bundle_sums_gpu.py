@@ -1,0 +1,74 @@
+"""Rays of the bundled adjoint meet in FP64, whatever shares a unit with them.
+
+Two cameras of the same geometry see one grid.  Some pixels hold V = 2^24 in the
+first and -V in the second; all others hold values of order 1.  Both cameras' units
+collect the same rays, so each large ray's values are formed alike twice and cancel
+in the FP64 accumulator to about V 2^-53, while what is left are the other pixels'
+values: the same as without the large pixels.  A partial sum of several rays in FP32
+would have lost it: V 2^-24 = 1.
+
+Tolerance: both results are rounded to FP32 once and their own FP32 products spread
+as in test_bundles_gpu, 1e-6; V's share of an FP64 rounding, 2^24 2^-53 times the
+few hundred terms of a voxel, lies below it."""
+import numpy as np
+import pytest
+
+from dotbar import dot_bar
+from paper_1812_03358_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+V = 2.0 ** 24
+CASES = {
+    # a wave per unit (576 units), a workgroup per unit (144, and blocks of pixels),
+    # hexagonal units, windows of 3, 4 and 5 voxels
+    "wave": (W.grid((24, 20, 32), 5.0), W.plenoptic_camera(144, 12, (2, 2), 64)),
+    "wave_30deg": (W.grid((40, 36, 38), 3.0), W.plenoptic_camera(192, 12, (2, 2), 80, 30.0)),
+    "workgroup": (W.grid((24, 20, 32), 5.0), W.plenoptic_camera(96, 6, (2, 2), 64)),
+    "workgroup_45deg": (W.grid((40, 36, 38), 3.0), W.plenoptic_camera(160, 10, (2, 2), 80, 45.0)),
+    "single": (W.grid((24, 20, 22), 4.0), W.single_lens_camera(53, (8, 8), 50, 30.0, det_v=41)),
+    "hex": (W.grid((30, 26, 28), 2.0), W.hex_plenoptic_camera(600, None, (2, 2), 60, 25.0)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_rays_of_a_unit_meet_in_fp64(name):
+    import torch
+
+    from paper_1812_03358_amd import ltm
+
+    g, cam = CASES[name]
+    plan = ltm.Plan(g, [cam, cam])
+    m = W.n_pixels(cam)
+    y = torch.from_numpy(W.uniform_random(2 * m, 91, 0.5, 1.0)).cuda().reshape(2, m)
+    big = torch.arange(7, m, 41, device="cuda")
+    y[:, big] = 0.0
+    want = plan.backproject(y.reshape(-1)).double()
+    y[0, big], y[1, big] = V, -V
+    got = plan.backproject(y.reshape(-1)).double()
+    err = float((got - want).norm() / want.norm())
+    print(f"{name}: {err:.2e}", flush=True)
+    assert float(want.norm()) > 0 and err < 1e-6
+
+
+@pytest.mark.parametrize("phi", [0.0, 33.0])
+def test_dot_identity_with_many_samples_per_cell(phi):
+    # 3000 samples in each of some ten cells a ray crosses: sums as long as the
+    # samples of a cell
+    import oracle
+    import torch
+
+    from paper_1812_03358_amd import ltm
+
+    g, cams = W.grid((12, 14, 10), 9.0), [W.plenoptic_camera(48, 6, (1, 1), 30000, phi)]
+    x, y = W.uniform_random(12 * 14 * 10, 93), W.uniform_random(48 * 48, 94, -1.0, 1.0)
+    plan = ltm.Plan(g, cams)
+    Ax = plan.project(torch.from_numpy(x).cuda()).cpu().numpy().astype(np.float64)
+    Aty = plan.backproject(torch.from_numpy(y).cuda()).cpu().numpy().astype(np.float64)
+    ref_Ax, ref_Aty = oracle.project(g, cams, x), oracle.backproject(g, cams, y)
+    assert np.linalg.norm(Aty - ref_Aty) <= 1e-5 * np.linalg.norm(ref_Aty)
+    x64, y64 = x.astype(np.float64), y.astype(np.float64)
+    gap = abs(np.dot(Ax, y64) - np.dot(x64, Aty)) / (np.linalg.norm(Ax) * np.linalg.norm(y64))
+    bar = dot_bar(x64, ref_Aty, y64, ref_Ax)
+    print(f"phi {phi}: gap {gap:.2e}, bar {bar:.2e}", flush=True)
+    assert gap <= bar
