@@ -910,6 +910,15 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_pow2(ConvWgrad a, int lw, in
 // current unit's MFMAs.  A workgroup owns (output tile, input tile, a
 // contiguous share of the units); wave w holds the 9 k-tiles of dy = w - 1 in
 // registers over its share and adds them into dw once.
+//
+// Rows of no whole chunk: an FP32 run ends after kRunUnits units and is added to the
+// share's sum, as the kernels that gather voxel by voxel, which such rows came from,
+// end one with each slice at the latest.  The second set of accumulators has to leave
+// three waves per SIMD their registers: 64 -> 32 channels at 64 x 64 x 60 101 us, with two
+// waves 132.  (Whole chunks keep to one run per share; a second set there, at rows of
+// 128, costs the network's training step 9%.)
+constexpr int kRunUnits = 8;
+
 template <int XC>
 struct WgradStage {
     static constexpr int NX8 = XC / 8;
@@ -1010,7 +1019,7 @@ __device__ __forceinline__ void wgrad_store(int y, bool full, const WgradStage<X
 }
 
 template <int XC, bool kRagged>
-__global__ __launch_bounds__(192) void k_conv_wgrad_rows(ConvWgrad a, int nshare)
+__global__ __launch_bounds__(192, kRagged && XC < 128 ? 3 : 1) void k_conv_wgrad_rows(ConvWgrad a, int nshare)
 {
     constexpr int XS = XC + 8;                   // LDS row stride (elements), padded against bank conflicts
     extern __shared__ uint4 sm4[];
@@ -1025,11 +1034,14 @@ __global__ __launch_bounds__(192) void k_conv_wgrad_rows(ConvWgrad a, int nshare
     const int nunits = a.D * chunks * a.H;
     const int u0 = (int)(((long long)nunits * blockIdx.y) / nshare);
     const int u1 = (int)(((long long)nunits * (blockIdx.y + 1)) / nshare);
-    f32x4 acc[3][3];
+    f32x4 acc[3][3], runs[kRagged ? 3 : 1][kRagged ? 3 : 1];
 #pragma unroll
     for (int s = 0; s < 3; ++s)
 #pragma unroll
-        for (int d = 0; d < 3; ++d) acc[s][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int d = 0; d < 3; ++d) {
+            acc[s][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (kRagged) runs[s][d] = acc[s][d];
+        }
     // unit -> (z, chunk, y), y fastest
     auto coords = [&](int unit, int& z, int& y, int& x0) {
         const int zc = unit / a.H;
@@ -1070,6 +1082,16 @@ __global__ __launch_bounds__(192) void k_conv_wgrad_rows(ConvWgrad a, int nshare
                     acc[s][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[d].v, B.v, acc[s][d], 0, 0, 0);
             }
         }
+        if constexpr (kRagged)
+            if ((unit - u0) % kRunUnits == kRunUnits - 1 || unit + 1 == u1) {
+#pragma unroll
+                for (int s = 0; s < 3; ++s)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        runs[s][d] += acc[s][d];
+                        acc[s][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
+            }
     }
     // D[4 kg + i][r]: output channel cot 16 + 4 kg + i, input channel
     // cit 16 + r of tap (dz = s - 1, dy = wave - 1, dx = d - 1)
@@ -1078,6 +1100,7 @@ __global__ __launch_bounds__(192) void k_conv_wgrad_rows(ConvWgrad a, int nshare
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             const int k = ((s * 3 + wave) * 3 + d) * cin + cit * 16 + r;
+            if constexpr (kRagged) acc[s][d] = runs[s][d];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int c = cot * 16 + 4 * kg + i;
@@ -1096,6 +1119,8 @@ hipError_t wgrad_rows(const ConvWgrad& a, hipStream_t s)
     // dw.  2, 3 and 5 of them: 16 -> 16 channels at 128^3 80, 114 (2.5) and 110 us (3),
     // 64 -> 64 at 32^3 82, 68 and 65, 32 -> 64 at 32^3 52, 44 and 48, 64 -> 32 at 64^3 95,
     // 78 and 95 us: beyond three the adds to one address, one after the other, cost more
+    // (four, in a training step: 60 us more over its ten layers of 64^3 and 32^3 voxels,
+    // though called over and over on one input they are faster)
     const size_t lds = (size_t)12 * 16 * (XC + 8) * sizeof(u16);
     const int shares = std::max(1, std::min(units, (XC == 128 ? 512 : 768) / tiles));
     if (a.W % XC)
@@ -1129,9 +1154,9 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_c1(ConvWgrad a, int nshare)
     const int u1 = (int)(((long long)nunits * (blockIdx.y + 1)) / nshare);
     for (int i = threadIdx.x; i < 3 * 16 * XS; i += 256) xs[i] = 0;
     for (int i = threadIdx.x; i < 27 * 16; i += 256) red[i] = 0.0f;
-    f32x4 acc[3];
+    f32x4 acc[3], runs[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int d = 0; d < 3; ++d) acc[d] = runs[d] = f32x4{0.f, 0.f, 0.f, 0.f};
     // a unit's loads are in flight while the one before is multiplied
     constexpr int NI = (9 * (XC + 2) + 255) / 256;
     u16 q[NI];
@@ -1153,34 +1178,44 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_c1(ConvWgrad a, int nshare)
                                    (threadIdx.x & 1) * 8, x0 + x < a.W);
     };
     if (u0 < u1) load(u0);
-    for (int unit = u0; unit < u1; ++unit) {
-        __syncthreads();   // the previous unit's fragments are read (and the clears done)
-        // input halo x0 - 1 + h: copy d (dx = d - 1) holds X[x0 + i + dx] at i = h - d
+    auto run = [&](int ua, int ub) {
+        for (int unit = ua; unit < ub; ++unit) {
+            __syncthreads();   // the previous unit's fragments are read (and the clears done)
+            // input halo x0 - 1 + h: copy d (dx = d - 1) holds X[x0 + i + dx] at i = h - d
 #pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            const int i = threadIdx.x + 256 * j, rr = i / (XC + 2), h = i - rr * (XC + 2);
-            if (rr >= 9) continue;
+            for (int j = 0; j < NI; ++j) {
+                const int i = threadIdx.x + 256 * j, rr = i / (XC + 2), h = i - rr * (XC + 2);
+                if (rr >= 9) continue;
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const int ix = h - d;
-                if ((unsigned)ix < (unsigned)XC) xs[(d * 16 + rr) * XS + ix] = q[j];
+                for (int d = 0; d < 3; ++d) {
+                    const int ix = h - d;
+                    if ((unsigned)ix < (unsigned)XC) xs[(d * 16 + rr) * XS + ix] = q[j];
+                }
+            }
+            if (threadIdx.x < XC * 2) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) dys[((threadIdx.x & 1) * 8 + j) * XS + (threadIdx.x >> 1)] = f.h[j];
+            }
+            __syncthreads();
+            if (unit + 1 < u1) load(unit + 1);
+            for (int gv = wave * 32; gv < XC; gv += 128) {
+                Frag A;
+                A.q = *reinterpret_cast<const uint4*>(dys + r * XS + gv + 8 * kg);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    Frag B;
+                    B.q = *reinterpret_cast<const uint4*>(xs + (d * 16 + r) * XS + gv + 8 * kg);
+                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.v, B.v, acc[d], 0, 0, 0);
+                }
             }
         }
-        if (threadIdx.x < XC * 2) {
+    };
+    for (int ua = u0; ua < u1; ua += kRunUnits) {
+        run(ua, min(ua + kRunUnits, u1));
 #pragma unroll
-            for (int j = 0; j < 8; ++j) dys[((threadIdx.x & 1) * 8 + j) * XS + (threadIdx.x >> 1)] = f.h[j];
-        }
-        __syncthreads();
-        if (unit + 1 < u1) load(unit + 1);
-        for (int gv = wave * 32; gv < XC; gv += 128) {
-            Frag A;
-            A.q = *reinterpret_cast<const uint4*>(dys + r * XS + gv + 8 * kg);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                Frag B;
-                B.q = *reinterpret_cast<const uint4*>(xs + (d * 16 + r) * XS + gv + 8 * kg);
-                acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.v, B.v, acc[d], 0, 0, 0);
-            }
+        for (int d = 0; d < 3; ++d) {
+            runs[d] += acc[d];
+            acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
     // D[4 kg + i][r]: output channel cot 16 + 4 kg + i, input row r (< 9),
@@ -1190,7 +1225,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_c1(ConvWgrad a, int nshare)
         for (int d = 0; d < 3; ++d)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (acc[d][i] != 0.0f) atomicAdd(&red[(r * 3 + d) * 16 + 4 * kg + i], acc[d][i]);
+                if (runs[d][i] != 0.0f) atomicAdd(&red[(r * 3 + d) * 16 + 4 * kg + i], runs[d][i]);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < 27 * 16; i += 256) {
@@ -1205,7 +1240,8 @@ hipError_t wgrad_c1(const ConvWgrad& a, hipStream_t s)
     const int cot = a.cout / 16;
     const int units = a.D * a.H * ((a.W + XC - 1) / XC);
     // shares of the units until 512 workgroups run; each adds 16 x 27 sums, one after
-    // the other at each address (128^3: 256 shares 120 us, 512 107, 1024 146)
+    // the other at each address (128^3: 256 shares 120 us, 512 107, 1024 146).  The FP32
+    // runs end within a share (kRunUnits), so that fewer shares do not lengthen them
     const int shares = std::max(1, std::min(units, 512 / cot));
     hipLaunchKernelGGL((k_conv_wgrad_c1<XC>), dim3(cot, shares), dim3(256), 0, s, a, shares);
     return hipGetLastError();
