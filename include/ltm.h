@@ -122,7 +122,8 @@ typedef struct ltm_camera {
  * of corner sums across the ray's dominant axis, so a step along that axis
  * flushes 4 corners, not 8 -- and, without bit 2, lets a camera whose rays run in
  * narrow bundles (those of one lenslet and aperture sample, or of a small block
- * of pixels, within about 2 voxels of each other) scatter whole bundles, which
+ * of pixels, within about 2 voxels of each other) scatter whole bundles, where
+ * they hold enough rays and samples for it (ltm_plan_adjoint_kind), which
  * takes no part of the tiling but this flag; bit 6 (with bit 3) makes the staggered starting
  * offsets even, so rays that advance half a voxel per sample along that axis
  * cross its cell planes on the same iterations.  Each workgroup
@@ -174,6 +175,11 @@ ltm_status ltm_plan_bind_workspace(ltm_plan* plan, void* ws, uint64_t bytes, voi
 
 ltm_status ltm_plan_get_tiling(const ltm_plan* plan, uint32_t direction, uint32_t camera,
                                ltm_tiling* out);
+/* How one camera's adjoint runs under its present tiling: ray by ray, or, with
+ * bit 5 and not bit 2 and where it is the faster way, in bundles, a wave or a
+ * workgroup to each. */
+enum { LTM_ADJOINT_RAYS = 0u, LTM_ADJOINT_WAVES = 1u, LTM_ADJOINT_WORKGROUPS = 2u };
+ltm_status ltm_plan_adjoint_kind(const ltm_plan* plan, uint32_t camera, uint32_t* kind);
 /* Replace one camera's tiling for one direction.  The plan becomes unbound:
  * query the workspace size and bind again. */
 ltm_status ltm_plan_set_tiling(ltm_plan* plan, uint32_t direction, uint32_t camera,

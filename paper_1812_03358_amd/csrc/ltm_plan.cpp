@@ -299,6 +299,57 @@ void camera_constants(const ltm_grid& g, const ltm_camera& c, CamDev& d)
     d.r2 = c.r_main_mm * c.r_main_mm;
 }
 
+// Whether units of so many rays (those that pass the main lens) are faster than the
+// ray-by-ray sweep, which a plane window without bundles gets.  A unit costs its set-up,
+// its folding and its atomics in every cell however few its rays, and a pass over every
+// cell however few their samples; the sweep's groups share bricks between lenslets
+// closer than a voxel, and few of them leave compute units idle.  Measured on 2000
+// cameras (12 to 1400 pixels across, 1 to 64 rays a pixel, grids of 12 to 210 voxels,
+// 0.05 to 20 samples per voxel): with these rules 4% (square lenslets) and 2% (hexagonal
+// ones, single lenses) above the faster of the two on average.
+bool bundles_pay(const ltm_grid& g, const ltm_camera& c, const CamDev& d, double units, double rays, double drift)
+{
+    const double per_voxel = (double)c.samples / d.n[d.dom], R = (double)c.rays_u * c.rays_v;
+    const bool along_axis = !oblique(c);
+    // few units of many rays: the longest one takes longer than the whole sweep, the
+    // more so the more samples it has (hexagonal, 980 rays: 98 units 202 us against 61,
+    // 340 231 against 434, with 13 samples per voxel 288 1018 against 321; 440 rays:
+    // 100 units 52 against 47, 252 73 against 94; 20 rays: 64 units 23 against 63.
+    // Square: 64 units of 628 rays 102 against 44, 96 114 against 757)
+    if (c.kind != LTM_SINGLE_LENS) {
+        const double few = c.kind == LTM_PLENOPTIC ? 4600.0 : (drift < 0.25 ? 3000.0 : 3700.0);
+        const double least = rays * rays / few;
+        if (units < std::max(least, std::min(512.0, least * per_voxel / 3.0))) return false;
+    }
+    // so many samples in a cell that the sweep's own cost per cell no longer counts
+    // (512^2, 32^2 lenslets, 128^3: 4 per voxel 480 against 535, 8 810 against 725, 32
+    // 2984 against 2036; at 8 degrees 3.0 against 4.4 ms; hexagonal, 8 per voxel 1.20
+    // against 1.16 ms, 20 2.69 against 1.99; 300^2 pixels of one ray: 20 per voxel 366
+    // against 369, 164 2.6 against 1.8 ms), or so few that a unit's rays have none in most
+    // of its cells (300^2 pixels of one ray, 100^3, 4 samples: 44 against 33, 16 55 against 52)
+    const bool single = c.kind == LTM_SINGLE_LENS;
+    if (units >= 512.0) {
+        if (along_axis && (single ? R == 1.0 && per_voxel > 16.0 : rays >= 100.0 && R <= 4.0 && per_voxel > 7.0))
+            return false;
+        if (single && R == 1.0 && per_voxel < 0.12) return false;
+    }
+    if (units <= 2048.0) return true;
+    // few rays a unit (2 x 2 pixels, 66^2 lenslets, 15 samples: 488 us against 140;
+    // 4 x 4 pixels, 39^2, 16: 208 against 107; 7 x 7, 114^2, 15: 507 against 321; 5 x 5, 4,
+    // 102^2 on 128^3 at 60 degrees: 378 against 293; 6 x 6 373 against 404; 4 x 4 head-on 329
+    // against 525; lenslets a quarter of a voxel apart, 7 x 7: 156 against 77), unless the
+    // sweep has few pixels (28^2, 4 x 4 pixels, 64 samples: 84 against 298); or few samples
+    // and many of an aperture (630^2, 9 x 9, 16, 4 samples a ray on 63^3: 275 against 174)
+    if (c.kind == LTM_PLENOPTIC) {
+        const double apart = std::fabs((double)d.Ac) / g.pitch_mm;
+        const bool few_pixels = rays >= 5.0 && (double)c.det_nu * c.det_nv < 1050.0 * rays;
+        const double least = R > 4.0 ? 32.0 : (R == 1.0 ? 0.0 : (along_axis ? 9.5 : 20.0));
+        if (few_pixels ? rays < 4.0 / apart : rays < std::max(least, (R == 1.0 ? 6.0 : 12.0) / apart)) return false;
+        if (!few_pixels && R > 4.0 && per_voxel < 0.12) return false;
+    }
+    return !single || rays >= 20.0;   // (blocks of 16 rays: 1524 us against 891)
+}
+
 // Units of the bundled adjoint (CamDev), or n_units = 0 where a unit's rays can
 // lie too far apart.  A wave sums a unit's samples in one cell layer into a
 // window of up to 5 x 4 voxels.  A window of W voxels holds any rays whose
@@ -351,30 +402,36 @@ void bundle_geometry(const ltm_grid& g, const ltm_camera& c, CamDev& d)
     };
     d.ub_shared = d.ub_rfast = 0;
     const int R = (int)(c.rays_u * c.rays_v);
+    double rays = 0.0;   // a unit's, as far as they pass the main lens
     if (c.kind == LTM_SINGLE_LENS) {
         // a block of pixels and part of an aperture row, or whole rows; the
         // cost of a sample falls with the rays that share a window's set-up,
-        // folding and atomics (about 60 rays' worth of work)
+        // folding and atomics (about 60 rays' worth of work), while there is a
+        // unit for every compute unit.  (Over 200 cameras of 40 to 800 pixels across
+        // and 1 to 64 rays a pixel, grids of 20^3 to 176^3: 1.14 times the time of the
+        // best of all shapes on average; with a unit for every SIMD, so smaller ones,
+        // 1.30, as each sends its own atomics: 88 x 104 pixels of 2 rays, 20^3 grid,
+        // blocks of 16 rays 110 us, of 64 43)
         static const int shapes[][2] = {{8, 8}, {4, 8}, {8, 4}, {4, 4}};
         double best = 0.0;
         for (const auto& sh : shapes)
             for (int r = 1; r <= R; ++r) {
                 if (r < (int)c.rays_u ? c.rays_u % r != 0 : r % c.rays_u != 0) continue;
-                const int rays = sh[0] * sh[1] * r;
-                if (rays < 16 || rays > kSharedRays) continue;
+                const int n = sh[0] * sh[1] * r;
+                if (n < 16 || n > kSharedRays) continue;
                 const int across = std::min(r, (int)c.rays_u) - 1, rows = r / (int)c.rays_u - 1;
                 const double step = window(spread(sh[0] - 1, 2.0 * across / c.rays_u),
                                            spread(sh[1] - 1, 2.0 * std::max(rows, 0) / c.rays_v));
-                // at least one unit per SIMD, or the others wait for the longest one
                 const double units = std::ceil((double)c.det_nu / sh[0]) * std::ceil((double)c.det_nv / sh[1]) *
                                      std::ceil((double)R / r);
-                const double cost = step * (rays + 60.0) * std::max(units, 1024.0);
+                const double cost = step * (n + 60.0) * std::max(units, 256.0);
                 if (step == 0.0 || (best > 0.0 && cost >= best)) continue;
                 best = cost;
+                rays = n;
                 d.ub_u = sh[0];
                 d.ub_v = sh[1];
                 d.ub_r = r;
-                d.ub_shared = rays > kUnitRays;
+                d.ub_shared = n > kUnitRays;
             }
         if (best == 0.0) return;
         d.nb_u = (int)((c.det_nu + d.ub_u - 1) / d.ub_u);
@@ -388,6 +445,7 @@ void bundle_geometry(const ltm_grid& g, const ltm_camera& c, CamDev& d)
         if (!std::isfinite(reach) || window(spread(std::min(ku - 1.0, 2.0 * reach), 0.0),
                                             spread(std::min(kv - 1.0, 2.0 * reach), 0.0)) == 0.0)
             return;
+        rays = std::min(3.1416 * reach * reach, ku * kv);
         d.ub_r = 1;
         d.nb_u = (int)c.mla_nu;
         d.nb_v = (int)c.mla_nv;
@@ -412,12 +470,11 @@ void bundle_geometry(const ltm_grid& g, const ltm_camera& c, CamDev& d)
     const uint64_t units = (uint64_t)d.nb_u * d.nb_v * ((R + d.ub_r - 1) / d.ub_r);
     d.n_units = units < (1ull << 20) ? (int)units : 0;
     // too few units for a wave each: their passes of 16 cells go to four waves (with
-    // blocks of 16 rays, 32^3 grid and 64^2 pixels of one ray: 31 -> 13 us)
-    if (units <= 512) d.ub_shared = 1;
-    // a hexagonal lenslet's unit is a thousand pixels' work, so few of them run longer
-    // than the ray-by-ray sweep (units: 72 156 against 63 us, 168 135 against 113, 360
-    // 165 against 161, 572 221 against 554)
-    if (c.kind == LTM_PLENOPTIC_HEX && units < 256) d.n_units = 0;
+    // blocks of 16 rays, 32^3 grid and 64^2 pixels of one ray: 31 -> 13 us; the shapes
+    // of 200 single-lens cameras that this and the price above choose: 1.14 times the
+    // best on average with 1024, 1.15 with 512)
+    if (units < 1024) d.ub_shared = 1;
+    if (!bundles_pay(g, c, d, (double)units, rays, std::max(drift[0], drift[1]))) d.n_units = 0;
 }
 
 // Tiling-dependent fields.
@@ -751,6 +808,15 @@ ltm_status ltm_plan_get_tiling(const ltm_plan* p, uint32_t dir, uint32_t cam, lt
     if (!p || !out) return fail(LTM_ERR_INVALID, "null argument");
     if (dir > 1 || cam >= p->cams.size()) return fail(LTM_ERR_INVALID, "bad direction or camera");
     *out = p->cams[cam].tiling[dir];
+    return LTM_OK;
+}
+
+ltm_status ltm_plan_adjoint_kind(const ltm_plan* p, uint32_t cam, uint32_t* kind)
+{
+    if (!p || !kind) return fail(LTM_ERR_INVALID, "null argument");
+    if (cam >= p->cams.size()) return fail(LTM_ERR_INVALID, "bad camera");
+    const CamHost& c = p->cams[cam];
+    *kind = !runs_bundles(c) ? LTM_ADJOINT_RAYS : (c.dev.ub_shared ? LTM_ADJOINT_WORKGROUPS : LTM_ADJOINT_WAVES);
     return LTM_OK;
 }
 

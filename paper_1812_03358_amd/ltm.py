@@ -22,6 +22,7 @@ LTM_ERR_NUMERIC = 3
 LTM_ERR_WORKSPACE = 4
 LTM_ERR_UNSUPPORTED = 5
 FORWARD, ADJOINT = 0, 1
+ADJOINT_RAYS, ADJOINT_WAVES, ADJOINT_WORKGROUPS = 0, 1, 2
 PSI_QUADRATIC, PSI_HYPERBOLA = 0, 1
 
 
@@ -93,6 +94,7 @@ _SIGS = {
     "ltm_plan_workspace_bytes": (ctypes.c_int, [_VP, ctypes.POINTER(_U64)]),
     "ltm_plan_bind_workspace": (ctypes.c_int, [_VP, _VP, _U64, _VP]),
     "ltm_plan_get_tiling": (ctypes.c_int, [_VP, _U32, _U32, ctypes.POINTER(Tiling)]),
+    "ltm_plan_adjoint_kind": (ctypes.c_int, [_VP, _U32, ctypes.POINTER(_U32)]),
     "ltm_plan_set_tiling": (ctypes.c_int, [_VP, _U32, _U32, ctypes.POINTER(Tiling)]),
     "ltm_plan_valid_rays": (ctypes.c_int, [_VP, _U32, ctypes.POINTER(_U64), _VP]),
     "ltm_plan_set_ray_subset": (ctypes.c_int, [_VP, _U32, _U32]),
@@ -277,6 +279,13 @@ class Plan:
         t = Tiling()
         _check(lib().ltm_plan_get_tiling(self._h, direction, camera, ctypes.byref(t)))
         return t
+
+    def adjoint_kind(self, camera: int = 0) -> int:
+        """How the camera's adjoint runs under its tiling: ADJOINT_RAYS,
+        ADJOINT_WAVES or ADJOINT_WORKGROUPS."""
+        k = ctypes.c_uint32()
+        _check(lib().ltm_plan_adjoint_kind(self._h, camera, ctypes.byref(k)))
+        return k.value
 
     def set_tiling(self, direction: int, camera: int, tiling, stream=None, rebind=True):
         if isinstance(tiling, dict):

@@ -20,10 +20,10 @@ pytestmark = pytest.mark.gpu
 
 V = 2.0 ** 24
 CASES = {
-    # a wave per unit (576 units), a workgroup per unit (144, and blocks of pixels),
+    # a wave per unit (1296 units), a workgroup per unit (144, and blocks of pixels),
     # hexagonal units, windows of 3, 4 and 5 voxels
-    "wave": (W.grid((24, 20, 32), 5.0), W.plenoptic_camera(144, 12, (2, 2), 64)),
-    "wave_30deg": (W.grid((40, 36, 38), 3.0), W.plenoptic_camera(192, 12, (2, 2), 80, 30.0)),
+    "wave": (W.grid((24, 20, 32), 5.0), W.plenoptic_camera(216, 18, (2, 2), 64)),
+    "wave_30deg": (W.grid((40, 36, 38), 3.0), W.plenoptic_camera(288, 18, (2, 2), 80, 30.0)),
     "workgroup": (W.grid((24, 20, 32), 5.0), W.plenoptic_camera(96, 6, (2, 2), 64)),
     "workgroup_45deg": (W.grid((40, 36, 38), 3.0), W.plenoptic_camera(160, 10, (2, 2), 80, 45.0)),
     "single": (W.grid((24, 20, 22), 4.0), W.single_lens_camera(53, (8, 8), 50, 30.0, det_v=41)),
@@ -39,6 +39,7 @@ def test_rays_of_a_unit_meet_in_fp64(name):
 
     g, cam = CASES[name]
     plan = ltm.Plan(g, [cam, cam])
+    assert plan.adjoint_kind() == (ltm.ADJOINT_WAVES if name.startswith("wave") else ltm.ADJOINT_WORKGROUPS)
     m = W.n_pixels(cam)
     y = torch.from_numpy(W.uniform_random(2 * m, 91, 0.5, 1.0)).cuda().reshape(2, m)
     big = torch.arange(7, m, 41, device="cuda")
@@ -60,9 +61,10 @@ def test_dot_identity_with_many_samples_per_cell(phi):
 
     from paper_1812_03358_amd import ltm
 
-    g, cams = W.grid((12, 14, 10), 9.0), [W.plenoptic_camera(48, 6, (1, 1), 30000, phi)]
-    x, y = W.uniform_random(12 * 14 * 10, 93), W.uniform_random(48 * 48, 94, -1.0, 1.0)
+    g, cams = W.grid((12, 14, 10), 9.0), [W.plenoptic_camera(72, 12, (2, 2), 30000, phi)]
+    x, y = W.uniform_random(12 * 14 * 10, 93), W.uniform_random(72 * 72, 94, -1.0, 1.0)
     plan = ltm.Plan(g, cams)
+    assert plan.adjoint_kind() != ltm.ADJOINT_RAYS
     Ax = plan.project(torch.from_numpy(x).cuda()).cpu().numpy().astype(np.float64)
     Aty = plan.backproject(torch.from_numpy(y).cuda()).cpu().numpy().astype(np.float64)
     ref_Ax, ref_Aty = oracle.project(g, cams, x), oracle.backproject(g, cams, y)
