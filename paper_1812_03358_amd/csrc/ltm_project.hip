@@ -1123,7 +1123,9 @@ __device__ __forceinline__ bool bundle_scatter(CamPtr cam, const UnitRays& P, in
     return true;
 }
 
-// Samples of up to 4 rays added to the accumulator one by one, 16 lanes a ray.
+// Samples of up to 4 rays added to the accumulator one by one, 16 lanes a ray.  A
+// corner of weight 0 is none of a sample's voxels (a value that is not finite would
+// leave NaN there).
 __device__ __forceinline__ void scatter_samples(CamPtr cam, const UnitRays& P, int i0, int i1,
                                                 double* __restrict__ xacc)
 {
@@ -1141,6 +1143,7 @@ __device__ __forceinline__ void scatter_samples(CamPtr cam, const UnitRays& P, i
             const int cx = k & 1, cy = (k >> 1) & 1, cz = k >> 2;
             const float wx = cx ? s.f[0] : 1.0f - s.f[0], wy = cy ? s.f[1] : 1.0f - s.f[1],
                         wz = cz ? s.f[2] : 1.0f - s.f[2];
+            if (wx == 0.0f || wy == 0.0f || wz == 0.0f) continue;
             unsafeAtomicAdd(&xacc[acc_index(c, (int)s.i[0] + cx, (int)s.i[1] + cy, (int)s.i[2] + cz)],
                             (double)(r.w * wz * wy * wx));
         }
