@@ -18,6 +18,16 @@ Accumulator plan_accumulators(const ltm_plan* p)
     return accumulators(p, reinterpret_cast<double*>(p->ws + p->accum_off), p->accum_words);
 }
 
+// Consecutive tiles that one work item covers, so that a camera's items number less
+// than 2^kTileBits: one, or several of a bundled adjoint, whose tiles are single
+// bundles (a ray-by-ray tile is a group of rays, whose size the tiling sets).
+uint32_t item_tiles(const CamDev& d)
+{
+    return d.bundle ? ((uint32_t)d.n_tiles >> kTileBits) + 1 : 1;
+}
+
+uint64_t item_count(const CamDev& d) { return ((uint64_t)d.n_tiles + item_tiles(d) - 1) / item_tiles(d); }
+
 struct Dir {
     std::vector<uint32_t> items;   // (batch camera << kTileBits) | tile, by decreasing cost
     size_t lds = 0;                // dynamic LDS of the persistent kernel
@@ -132,18 +142,18 @@ ltm_status ltm_batch_create(ltm_plan* const* plans, uint32_t n_plans, ltm_batch*
     }
     uint64_t off = 0;
     for (int d = 0; d < 2; ++d) {
-        std::vector<std::pair<double, uint32_t>> order;   // (cost per tile, batch camera)
+        std::vector<std::pair<double, uint32_t>> order;   // (cost per item, batch camera)
         size_t lds = 0;
         for (size_t q = 0; q < b->pcs.size(); ++q) {
             const ltm_plan* p = b->plans[b->pcs[q].first];
             const CamDev dv = bound_dev(p, p->cams[b->pcs[q].second], d);
-            if ((uint64_t)dv.n_tiles >= (1ull << kTileBits)) {
+            if (item_count(dv) >= (1ull << kTileBits)) {
                 delete b;
                 return fail(LTM_ERR_INVALID, "a camera has more than 2^20 tiles");
             }
             const double rays = dv.bundle ? (dv.ub_shared ? 1.0 : kThreads / 64) * dv.ub_u * dv.ub_v * dv.ub_r
                                           : (double)dv.items_per_split * dv.ru * dv.rv;
-            order.push_back({rays * dv.S, (uint32_t)q});
+            order.push_back({rays * dv.S * item_tiles(dv), (uint32_t)q});
             lds = std::max(lds, march_lds_bytes(dv, d));
             b->dir[d].kinds |= dv.bundle ? 2 : 1;
         }
@@ -152,7 +162,8 @@ ltm_status ltm_batch_create(ltm_plan* const* plans, uint32_t n_plans, ltm_batch*
         for (auto& o : order) {
             const ltm_plan* p = b->plans[b->pcs[o.second].first];
             const CamDev dv = bound_dev(p, p->cams[b->pcs[o.second].second], d);
-            for (int t = 0; t < dv.n_tiles; ++t) b->dir[d].items.push_back((o.second << kTileBits) | (uint32_t)t);
+            const uint32_t n = (uint32_t)item_count(dv);
+            for (uint32_t t = 0; t < n; ++t) b->dir[d].items.push_back((o.second << kTileBits) | t);
         }
         b->dir[d].lds = lds;
         b->cams_off[d] = off;
@@ -214,6 +225,7 @@ ltm_status ltm_batch_bind(ltm_batch* b, void* ws, uint64_t bytes, const float* c
             bc.x = d == LTM_FORWARD ? x_in[pc.first] : x_out[pc.first];
             bc.y = y[pc.first];
             bc.xacc = accumulator_of(plan_accumulators(p), bc.cam);
+            bc.item_tiles = (int)item_tiles(bc.cam);
             b->host_cams[d].push_back(bc);
         }
         b->dir[d].blocks = cus * batch_blocks_per_cu(d, b->dir[d].kinds, b->dir[d].lds);

@@ -106,6 +106,7 @@ struct BatchCam {
     const float* x;
     float* y;
     double* xacc;
+    int item_tiles;       // bundled adjoints: consecutive tiles of one work item
 };
 // The adjoint's FP64 accumulators, N words each: [z][y][x], and [y][x][z] for
 // bundled cameras that look along z (their atomics walk 16 voxels of a column at a
@@ -116,7 +117,7 @@ struct Accumulator {
 };
 constexpr int kUnitRays = 128;    // rays a wave of the bundled adjoint holds at once
 constexpr int kSharedRays = 576;  // rays a workgroup of it holds at once (4 workgroups share a CU's LDS)
-constexpr int kTileBits = 20;   // work item = (batch camera << 20) | tile
+constexpr int kTileBits = 20;   // work item = (batch camera << 20) | tile (or run of tiles)
 
 struct CamHost {
     ltm_camera desc;

@@ -468,7 +468,7 @@ void bundle_geometry(const ltm_grid& g, const ltm_camera& c, CamDev& d)
         }
     }
     const uint64_t units = (uint64_t)d.nb_u * d.nb_v * ((R + d.ub_r - 1) / d.ub_r);
-    d.n_units = units < (1ull << 20) ? (int)units : 0;
+    d.n_units = units < (1ull << 30) ? (int)units : 0;
     // too few units for a wave each: their passes of 16 cells go to four waves (with
     // blocks of 16 rays, 32^3 grid and 64^2 pixels of one ray: 31 -> 13 us; the shapes
     // of 200 single-lens cameras that this and the price above choose: 1.14 times the

@@ -1543,7 +1543,9 @@ __global__ __launch_bounds__(kThreads, kSweep == Sweep::bundles || kSweep == Swe
             march_tile<false>(bc.cam, tile, bc.x, bc.y, nullptr, smem, wsum);
         } else {
             if (kSweep == Sweep::bundles || (kSweep == Sweep::mixed && bc.cam.bundle)) {
-                bundle_tile((CamPtr)(uintptr_t)&bc.cam, tile, bc.y, bc.xacc, reinterpret_cast<float4*>(smem), wsum);
+                const int t0 = tile * bc.item_tiles, t1 = min(t0 + bc.item_tiles, bc.cam.n_tiles);
+                for (int t = t0; t < t1; ++t)
+                    bundle_tile((CamPtr)(uintptr_t)&bc.cam, t, bc.y, bc.xacc, reinterpret_cast<float4*>(smem), wsum);
             } else if constexpr (kSweep != Sweep::bundles) {
                 march_tile<true>(bc.cam, tile, bc.y, nullptr, bc.xacc, smem, wsum);
             }

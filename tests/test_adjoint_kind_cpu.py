@@ -61,6 +61,9 @@ CASES = {
     "lenslet_32x32": (_pl(16, 32, (2, 2), 256), WAVES),
     "hex_few": (_hex(200, (2, 2), 200), RAYS),
     "hex_coarse_few": (_hex(200, (2, 2), 200, coarse=6), GROUPS),
+    # 2^20 units and more
+    "units_2_20": (_pl(128, 16, (8, 8), 256), WAVES),
+    "units_over_2_20": ((W.grid(64, 4.0), W.single_lens_camera(4096, (8, 8), 64, det_v=3072)), GROUPS),
     # a wave or a workgroup to a unit
     "units_1020": ((W.grid(24, 5.0), W.plenoptic_camera(144, 12, (7, 1), 64)), GROUPS),
     "units_1024": ((W.grid(24, 5.0), W.plenoptic_camera(192, 16, (2, 2), 64)), WAVES),

@@ -110,6 +110,23 @@ def test_batch_of_kinds(ltm, names):
         assert float((o.double() - want).norm() / want.norm()) < 1e-6
 
 
+def test_batch_of_more_units_than_items(ltm):
+    # 1.6 million units: a batch camera's work items number less than 2^20, so an item
+    # covers two of them
+    import torch
+
+    plan = ltm.Plan(W.grid(64, 4.0), [W.single_lens_camera(4096, (8, 8), 3, det_v=3072)])
+    assert plan.adjoint_kind() == GROUPS
+    x, y = torch.rand(plan.n_voxels, device="cuda"), torch.empty(plan.n_meas, device="cuda")
+    out = torch.empty_like(x)
+    ltm.Batch([plan], [x], [y], [out]).sweep()
+    want = plan.backproject(plan.project(x)).double()
+    assert float((out.double() - want).norm() / want.norm()) < 1e-6
+    plan.set_tiling(ltm.ADJOINT, 0, {"order": 26})
+    rays = plan.backproject(y).double()
+    assert float((out.double() - rays).norm() / rays.norm()) < 1e-6
+
+
 def test_one_accumulator_for_both_orientations(ltm):
     # between 2^22 and 2^23 voxels the fixed accumulator of the allocation-free entry
     # point holds one of the two that these cameras call for
