@@ -83,8 +83,9 @@ struct CamDev {
     // over nb_u x nb_v blocks (hexagonal cameras: blocks are lenslets, whose
     // light falls around ub_cu, ub_cv pixels per lenslet coordinate from the
     // detector's centre); ub_shared: a workgroup, not a wave, takes a unit;
-    // ub_rfast: consecutive units are aperture samples of one block
-    int bundle, dom, dom_sign, ub_u, ub_v, ub_r, ub_shared, ub_rfast, nb_u, nb_v, n_units;
+    // ub_rfast: consecutive units are aperture samples of one block; ub_rot: by how
+    // many blocks each row of them is turned against the one before
+    int bundle, dom, dom_sign, ub_u, ub_v, ub_r, ub_shared, ub_rfast, ub_rot, nb_u, nb_v, n_units;
     float ub_cu, ub_cv;
     int acc_zfast;        // adjoint: the accumulator is [y][x][z] (Accumulator::z), not [z][y][x]
     int groups_per_cu;    // 0, or the most workgroups one CU may hold (LDS reservation)

@@ -1200,7 +1200,7 @@ __device__ __forceinline__ void bundle_unit(CamPtr cam, int unit, const float* _
     for (int base = 0; base < total;) {
         const CamDev& c = fresh(cam);
         const int npx = c.ub_u * c.ub_v;
-        const int bv = blk / c.nb_u, bu = blk - bv * c.nb_u;
+        const int bv = blk / c.nb_u, bu = (blk - bv * c.nb_u + c.ub_rot * bv) % c.nb_u;
         int iu0 = bu * c.ub_u, iv0 = bv * c.ub_v;
         Lenslet L = {0.0f, 0.0f, c.Ag, c.Bg, c.Lg};
         if (c.kind == LTM_PLENOPTIC) {

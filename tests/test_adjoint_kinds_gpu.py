@@ -127,6 +127,30 @@ def test_batch_of_more_units_than_items(ltm):
     assert float((out.double() - rays).norm() / rays.norm()) < 1e-6
 
 
+def test_time_of_rows_of_a_power_of_two_blocks(ltm):
+    # rows of 128 blocks keep no XCD to the same columns: 1024^2 pixels take no longer
+    # than 1016^2 do, but for their number (twice as long before)
+    import torch
+
+    def ms(det):
+        plan = ltm.Plan(W.grid(100, 1.0), [W.single_lens_camera(det, (4, 4), 200)])
+        assert plan.adjoint_kind() != RAYS
+        y, x = torch.rand(plan.n_meas, device="cuda"), torch.empty(plan.n_voxels, device="cuda")
+        t = []
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            plan.backproject(y, x)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t)
+
+    a, b = ms(1016), ms(1024)
+    print(f"1016: {a:.2f} ms, 1024: {b:.2f} ms", flush=True)
+    assert b < 1.5 * a
+
+
 def test_one_accumulator_for_both_orientations(ltm):
     # between 2^22 and 2^23 voxels the fixed accumulator of the allocation-free entry
     # point holds one of the two that these cameras call for
