@@ -160,7 +160,9 @@ void ltm_plan_destroy(ltm_plan* plan);
 /* N = nx*ny*nz voxels and M = total pixels over all cameras. */
 ltm_status ltm_plan_sizes(const ltm_plan* plan, uint64_t* n_voxels, uint64_t* n_meas);
 
-/* Device workspace the plan needs (tile and brick tables), in bytes. */
+/* Device workspace the plan needs, in bytes: tile and brick tables (none for an
+ * adjoint in bundles) and one or two FP64 volumes, two where bundled cameras that look
+ * along z, whose adjoints are faster into one ordered along z, and others share the plan. */
 ltm_status ltm_plan_workspace_bytes(const ltm_plan* plan, uint64_t* bytes);
 
 /* Bind a caller-owned device workspace and fill its tables on `stream`.  The

@@ -550,7 +550,8 @@ void layout(ltm_plan* p)
             CamDev tmp = c.dev;
             apply_tiling(p->grid, c.desc, c.tiling[dir], tmp, c.n_tiles[dir], c.max_chunks[dir],
                          c.chunk_floor[dir]);
-            c.tiles_off[dir] = off;
+            c.tiles_off[dir] = c.bricks_off[dir] = off;
+            if (dir == LTM_ADJOINT && runs_bundles(c)) continue;   // bundles use no tables
             off = align256(off + sizeof(TileRec) * (uint64_t)c.n_tiles[dir]);
             c.bricks_off[dir] = off;
             off = align256(off + sizeof(BrickRec) * (uint64_t)c.n_tiles[dir] * c.max_chunks[dir]);
@@ -781,7 +782,7 @@ ltm_status ltm_plan_bind_workspace(ltm_plan* p, void* ws, uint64_t bytes, void* 
         for (int dir = 0; dir < 2; ++dir) {
             for (;;) {
                 const CamDev d = bound_dev(p, c, dir);
-                if (d.bundle) break;   // bundles use no tile or brick tables
+                if (d.bundle) break;   // no tables (layout)
                 hipError_t e = launch_setup(d, dir, s);
                 if (e != hipSuccess) return hip_fail(e, "tile setup");
                 if (!c.adapt[dir] || c.tiling[dir].chunk_mm * 0.5 < c.chunk_floor[dir] * 0.999) break;
