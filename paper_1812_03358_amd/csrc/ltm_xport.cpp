@@ -638,7 +638,7 @@ ltm_status ltm_xport_create(const ltm_grid* g, const ltm_camera* c, uint32_t bas
     place(t->off_cst_w, t->cst.w.size() * 4);
     place(t->off_btt_s, t->btt.start.size() * 4);
     place(t->off_btt_w, t->btt.w.size() * 4);
-    place(t->off_mid, mid / c->rays_v * ng * 4);
+    place(t->off_mid, mid * 4);   // the room of one row per group at most is used
     if (rot) place_shears(t, g, off);
     t->ws_bytes = off;
     add_turn(t, qm, gq);
