@@ -238,7 +238,7 @@ ltm_status ltm_backproject_noalloc(ltm_plan* plan, const float* y, float* x, voi
  * be used.  For every camera and direction, ltm_autotune runs each candidate
  * on a one-camera copy of the plan (the full operator, whatever view subset
  * the plan is set to), on x (forward) or on the camera's block of y
- * (adjoint); a candidate whose output differs from the current tiling's by
+ * (adjoint; tilings under which it runs in bundles are one candidate); a candidate whose output differs from the current tiling's by
  * more than 1e-6 relative L2 is rejected before it is timed.  The survivors
  * are timed with HIP events on `stream` (median of `reps` runs after one
  * untimed run).  Stage 1 searches tile size, lane order flags, slab depth

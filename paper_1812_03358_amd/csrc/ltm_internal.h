@@ -182,6 +182,14 @@ hipError_t launch_batch(const BatchCam* cams, const uint32_t* items, uint32_t n_
                         unsigned int* counter, int dir, int kinds, int blocks, size_t lds, hipStream_t s);
 int batch_blocks_per_cu(int dir, int kinds, size_t lds);
 
+// whether a camera's adjoint runs in bundles under a tiling: its rays are narrow and
+// many enough, and the tiling asks for plane windows in FP64.  No other part of the
+// tiling changes the launch then.
+inline bool bundled(const CamDev& d, const ltm_tiling& t)
+{
+    return d.n_units > 0 && (t.order & 32) && !(t.order & 4);
+}
+
 // tiling limits (ltm_plan.cpp); sets the error message on failure
 ltm_status check_tiling(const ltm_grid& g, const ltm_camera& c, const ltm_tiling& t);
 

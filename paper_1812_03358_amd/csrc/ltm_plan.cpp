@@ -525,13 +525,7 @@ void apply_tiling(const ltm_grid& g, const ltm_camera& c, const ltm_tiling& t, C
     max_chunks = d.max_chunks;
 }
 
-// The camera's adjoint runs in bundles: its rays are narrow enough, and its
-// tiling asks for plane windows in FP64.
-bool runs_bundles(const CamHost& c)
-{
-    const uint32_t order = c.tiling[LTM_ADJOINT].order;
-    return c.dev.n_units > 0 && (order & 32) && !(order & 4);
-}
+bool runs_bundles(const CamHost& c) { return bundled(c.dev, c.tiling[LTM_ADJOINT]); }
 
 // bit 0: some camera adds into a [z][y][x] accumulator, bit 1: some camera is
 // faster into a [y][x][z] one

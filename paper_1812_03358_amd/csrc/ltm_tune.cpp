@@ -6,7 +6,8 @@
 // FP64 sums only change order), and is timed with HIP events.  The search
 // has two stages: tile shape, lane order, slab depth and brick size at full
 // occupancy, then the occupancy cap (workgroups per CU) for the three fastest
-// shapes.  Results are cached in a text file keyed by the GPU architecture,
+// shapes.  An adjoint that runs in bundles takes nothing of a tiling but its
+// plane-window bit, so all such tilings count as one.  Results are cached in a text file keyed by the GPU architecture,
 // the grid and the camera descriptor.
 #include <algorithm>
 #include <cmath>
@@ -121,9 +122,16 @@ uint32_t rays_of(const ltm_camera& c)
     return c.rays_u * c.rays_v * (c.kind == LTM_PLENOPTIC_HEX ? 9u : 1u);
 }
 
-// Stage-1 candidates: tile shape, lane order flags, slab depth and brick.
-std::vector<ltm_tiling> shape_candidates(const ltm_grid& g, const ltm_camera& c, int dir)
+// Two tilings under which the camera's adjoint is the same launch of bundles.
+bool same_bundles(const CamHost& c, int dir, const ltm_tiling& a, const ltm_tiling& b)
 {
+    return dir == LTM_ADJOINT && bundled(c.dev, a) && bundled(c.dev, b);
+}
+
+// Stage-1 candidates: tile shape, lane order flags, slab depth and brick.
+std::vector<ltm_tiling> shape_candidates(const ltm_grid& g, const CamHost& cam, int dir)
+{
+    const ltm_camera& c = cam.desc;
     std::vector<ltm_tiling> out;
     const bool pl = c.kind == LTM_PLENOPTIC;
     const uint64_t k = pl ? (uint64_t)(c.det_nu / c.mla_nu) * (c.det_nv / c.mla_nv) : 1;
@@ -138,8 +146,9 @@ std::vector<ltm_tiling> shape_candidates(const ltm_grid& g, const ltm_camera& c,
         x.brick_floats = brick;
         x.chunk_mm = chunk * g.pitch_mm;
         if (check_tiling(g, c, x) != LTM_OK) return;
+        // two group sizes gave one split, or two tilings the same bundles
         for (const ltm_tiling& y : out)
-            if (std::memcmp(&x, &y, sizeof(x)) == 0) return;    // two group sizes gave one split
+            if (std::memcmp(&x, &y, sizeof(x)) == 0 || same_bundles(cam, dir, x, y)) return;
         out.push_back(x);
     };
     if (dir == LTM_FORWARD) {
@@ -266,7 +275,7 @@ ltm_status camera_bytes(const ltm_plan* p, uint32_t ci, uint64_t& tables, uint64
     for (int dir = 0; dir < 2; ++dir) {
         ltm_tiling other = c.tiling[1 - dir];
         ltm_plan_set_tiling(sub, (uint32_t)(1 - dir), 0, &other);
-        std::vector<ltm_tiling> cands = shape_candidates(p->grid, c.desc, dir);
+        std::vector<ltm_tiling> cands = shape_candidates(p->grid, c, dir);
         cands.push_back(c.tiling[dir]);
         uint64_t most = 0;
         for (const ltm_tiling& t : cands) {
@@ -301,7 +310,7 @@ ltm_status ltm_autotune_candidates(const ltm_plan* p, uint32_t dir, uint32_t cam
 {
     if (!p || !count) return fail(LTM_ERR_INVALID, "null argument");
     if (dir > 1 || cam >= p->cams.size()) return fail(LTM_ERR_INVALID, "bad direction or camera");
-    std::vector<ltm_tiling> c = shape_candidates(p->grid, p->cams[cam].desc, (int)dir);
+    std::vector<ltm_tiling> c = shape_candidates(p->grid, p->cams[cam], (int)dir);
     *count = (uint32_t)c.size();
     if (out)
         for (uint32_t i = 0; i < std::min<uint32_t>(capacity, (uint32_t)c.size()); ++i) out[i] = c[i];
@@ -372,6 +381,7 @@ ltm_status ltm_autotune(ltm_plan* p, const float* x, const float* y, void* ws, u
             // every candidate passes the parity gate before it is timed
             auto consider = [&](const ltm_tiling& t, double& t_ms) -> ltm_status {
                 t_ms = INFINITY;
+                if (same_bundles(c, dir, t, current)) return LTM_OK;   // timed already
                 if (check_tiling(p->grid, c.desc, t) != LTM_OK) {
                     clear_error();
                     return LTM_OK;
@@ -401,7 +411,7 @@ ltm_status ltm_autotune(ltm_plan* p, const float* x, const float* y, void* ws, u
                 if ((st = consider(cached, t_ms)) != LTM_OK) return st;
             } else {
                 std::vector<std::pair<double, ltm_tiling>> timed;
-                for (const ltm_tiling& t : shape_candidates(p->grid, c.desc, dir)) {
+                for (const ltm_tiling& t : shape_candidates(p->grid, c, dir)) {
                     if ((st = consider(t, t_ms)) != LTM_OK) return st;
                     if (std::isfinite(t_ms)) timed.push_back({t_ms, t});
                 }
@@ -413,7 +423,7 @@ ltm_status ltm_autotune(ltm_plan* p, const float* x, const float* y, void* ws, u
                 for (size_t i = 0; i < timed.size() && i < (size_t)kOccupancyShapes; ++i)
                     for (uint32_t cap : kOccupancyCaps) {
                         ltm_tiling t = timed[i].second;
-                        if (t.groups_per_cu == cap) continue;
+                        if (t.groups_per_cu == cap || same_bundles(c, dir, t, t)) continue;
                         t.groups_per_cu = cap;
                         if ((st = consider(t, t_ms)) != LTM_OK) return st;
                     }

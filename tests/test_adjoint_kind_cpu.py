@@ -81,6 +81,19 @@ def test_kind(ltm, name):
         assert [plan.adjoint_kind(k) for k in range(2)] == [RAYS, kind]
 
 
+@pytest.mark.parametrize("name", ["plenoptic_128", "single_64_rays", "lenslet_3x3", "hex_few"])
+def test_autotune_candidates(ltm, name):
+    # tilings that are one launch of bundles are one candidate
+    from paper_1812_03358_amd import autotune
+
+    (g, cam), kind = CASES[name]
+    plan = ltm.Plan(g, [cam], bind=False)
+    orders = [c["order"] for c in autotune.candidates(plan, 0, ltm.ADJOINT)]
+    window = sum(1 for o in orders if o & 32)
+    assert window == 1 if kind != RAYS else window > 8
+    assert sum(1 for o in orders if not o & 32) >= 8
+
+
 def test_errors(ltm):
     g, cam = _pl(64, 16, (2, 2), 256)
     plan = ltm.Plan(g, [cam], bind=False)
