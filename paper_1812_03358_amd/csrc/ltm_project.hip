@@ -18,6 +18,7 @@
 // cameras whose rays run in narrow bundles (k_bundle) uses neither tiles nor
 // bricks: a wave sums one bundle's rays in registers.
 #include "ltm_internal.h"
+#include "ltm_parts.h"
 
 #include <algorithm>
 #include <cfloat>
@@ -1150,22 +1151,21 @@ __device__ __forceinline__ void scatter_samples(CamPtr cam, const UnitRays& P, i
     }
 }
 
-// The collected rays P[0, cnt): all at once if their windows hold them,
-// otherwise in halves, down to 4 rays, whose samples then go one by one.
+// The collected rays P[0, cnt): all at once if their windows hold them, otherwise in
+// halves, down to 4 rays, whose samples then go one by one; then in larger parts again.
 __device__ __forceinline__ void bundle_flush(CamPtr cam, const UnitRays& P, int cnt,
                                              double* __restrict__ xacc)
 {
-    int len = (cnt + 3) & ~3;
-    for (int i = 0; i < cnt;) {
-        const int end = min(i + len, cnt);
+    for (Parts part{(cnt + 3) >> 2}; !part.done();) {
+        const int i = 4 * part.begin(), end = min(4 * part.end(), cnt);
         if (!bundle_scatter(cam, P, i, end, xacc)) {
-            if (len > 4) {
-                len = ((len >> 1) + 3) & ~3;
+            if (part.end() - part.begin() > 1) {
+                part.halve();
                 continue;
             }
             if (P.first == 0) scatter_samples(cam, P, i, end, xacc);
         }
-        i = end;
+        part.next();
     }
 }
 
