@@ -339,8 +339,10 @@ __device__ __forceinline__ void conv_epilogue(const ConvFwd& a, const f32x4 (&ac
 // wait for the halo.  So a thread stages one (x, channel group) of many rows, all
 // their loads in flight; the steps are unrolled, their LDS offsets immediates from
 // a few lane bases; the weights' addresses are scalar.  WN is what reads the
-// weights seldom enough: 64 -> 32 channels at 64^3, WN 1 112 us, WN 2 70 us.  Of
-// the kernel with one staging load in flight, scattered stores and table offsets
+// weights seldom enough: 64 -> 32 channels at 64^3, WN 1 112 us, WN 2 70 us.  With
+// eight channel tiles that is 4 (WN 1, 2, 4 at 64^3: 16 -> 128 channels 89, 65,
+// 57 us, 32 -> 128 97, 73, 70 us, 64 -> 128 429, 238, 150 us; 32^3 and 128^3 alike).
+// Of the kernel with one staging load in flight, scattered stores and table offsets
 // to this one: 16 -> 16 channels at 128^3 82 -> 61 us, 32 -> 16 163 -> 104, 64 -> 32
 // at 64^3 137 -> 70 (418 TFLOP/s), 32 -> 32 at 64^3 46 -> 24 us.
 template <int CIN, int NT, int TZ, int WN>
@@ -1673,11 +1675,11 @@ hipError_t nn_conv_fwd(const ConvFwd& a, int ks, hipStream_t s)
         case 16 * 16 + 1: LTM_TILE(16, 1, 8, 1);
         case 16 * 16 + 2: LTM_TILE(16, 2, 8, 1);
         case 16 * 16 + 4: LTM_TILE(16, 4, 8, 1);
-        case 16 * 16 + 8: LTM_TILE(16, 8, 4, 2);
+        case 16 * 16 + 8: LTM_TILE(16, 8, 4, 4);
         case 32 * 16 + 1: LTM_TILE(32, 1, 4, 1);
         case 32 * 16 + 2: LTM_TILE(32, 2, 4, 2);
         case 32 * 16 + 4: LTM_TILE(32, 4, 4, 4);
-        case 32 * 16 + 8: LTM_TILE(32, 8, 4, 2);
+        case 32 * 16 + 8: LTM_TILE(32, 8, 4, 4);
         case 64 * 16 + 1: LTM_TILE(64, 1, 2, 1);
         case 64 * 16 + 2: LTM_TILE(64, 2, 2, 2);
         case 64 * 16 + 4: LTM_TILE(64, 4, 2, 2);
