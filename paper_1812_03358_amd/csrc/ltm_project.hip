@@ -774,10 +774,10 @@ __device__ __forceinline__ void scatter_global(const March& mr, int m0, int m1, 
 // bricks or barriers.
 //
 // Against the ray-by-ray adjoint (scatter_lds_window) of the same cameras, ms:
-// plenoptic 1024^2 on 128^3 0.80 -> 0.59 head-on, 1.46 -> 0.84 at 30 degrees,
-// 3.79 -> 1.02 at 45; hexagonal 2048^2 on 100^3 4.77 -> 2.26, 7.33 -> 3.48 at 20
-// degrees; single-lens 461 x 400 with 64 samples per pixel 8.07 -> 3.98 at 30
-// degrees, 5.32 -> 3.21 head-on.  The FP64 sums are what keeps it from more: with
+// plenoptic 1024^2 on 128^3 0.80 -> 0.55 head-on, 1.46 -> 0.69 at 30 degrees,
+// 3.79 -> 0.75 at 45; hexagonal 2048^2 on 100^3 4.77 -> 2.25, 7.33 -> 3.45 at 20
+// degrees; single-lens 461 x 400 with 64 samples per pixel 8.07 -> 4.03 at 30
+// degrees, 5.32 -> 3.22 head-on.  The FP64 sums are what keeps it from more: with
 // FP32 sums over some 32 samples of the unit's rays it took 0.47, 0.70, 0.78, 1.88,
 // 2.87, 3.13 and 2.52, but different rays have always met in FP64.
 struct BundleRay {
@@ -859,7 +859,8 @@ __device__ __forceinline__ double fold16(double x, double y)
 // As values known from the kernel's start on, what derives from them (floats of the
 // sizes, reciprocals, edges) is computed there once and then waits in scratch memory
 // while the windows fill the registers (248 bytes a lane instead of 100: the head-on
-// 128^3 camera 638 us against 591, with an image of zeros 55 us against 33).
+// 128^3 camera 638 us against 591 when this was measured, 547 now; with an image of
+// zeros 55 us against 33).
 typedef const __attribute__((address_space(4))) CamDev* CamPtr;
 
 __device__ __forceinline__ const CamDev& fresh(CamPtr cam)
