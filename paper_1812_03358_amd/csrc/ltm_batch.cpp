@@ -32,7 +32,7 @@ struct Dir {
     std::vector<uint32_t> items;   // (batch camera << kTileBits) | tile, by decreasing cost
     size_t lds = 0;                // dynamic LDS of the persistent kernel
     int blocks = 0;                // persistent workgroups
-    int kinds = 0;                 // bit 0: cameras scattered ray by ray, bit 1: in bundles
+    int kinds = 0;                 // bit 0: cameras scattered ray by ray, 1: in bundles by waves, 2: by workgroups
     uint64_t items_off = 0;
 };
 
@@ -155,7 +155,7 @@ ltm_status ltm_batch_create(ltm_plan* const* plans, uint32_t n_plans, ltm_batch*
                                           : (double)dv.items_per_split * dv.ru * dv.rv;
             order.push_back({rays * dv.S * item_tiles(dv), (uint32_t)q});
             lds = std::max(lds, march_lds_bytes(dv, d));
-            b->dir[d].kinds |= dv.bundle ? 2 : 1;
+            b->dir[d].kinds |= !dv.bundle ? 1 : (dv.ub_shared ? 4 : 2);
         }
         std::stable_sort(order.begin(), order.end(),
                          [](const auto& a, const auto& c) { return a.first > c.first; });

@@ -1263,11 +1263,12 @@ __device__ __forceinline__ void bundle_unit(CamPtr cam, int unit, const float* _
 }
 
 // The units of one tile: one shared by the workgroup, or one per wave.
+template <bool kShared>
 __device__ __forceinline__ void bundle_tile(CamPtr c, int tile, const float* __restrict__ y,
                                             double* __restrict__ xacc, float4* lds, int* wsum)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (fresh(c).ub_shared)
+    if constexpr (kShared)
         bundle_unit<true>(c, tile, y, xacc, lds, wsum);
     else
         bundle_unit<false>(c, tile * (kThreads / 64) + wave, y, xacc,
@@ -1281,12 +1282,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_bundle(CamDev, const float* __r
     const CamPtr c = (CamPtr)__builtin_amdgcn_kernarg_segment_ptr();   // the first argument, as it lies there
     extern __shared__ float4 rays[];
     __shared__ int wsum[kThreads / 64];
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if constexpr (kShared)
-        bundle_unit<true>(c, blockIdx.x, y, xacc, rays, wsum);
-    else
-        bundle_unit<false>(c, (int)blockIdx.x * (kThreads / 64) + wave, y, xacc,
-                           rays + wave * 2 * kUnitRays, wsum);
+    bundle_tile<kShared>(c, blockIdx.x, y, xacc, rays, wsum);
 }
 
 // ---------------------------------------------------------------- A x, A^T y
@@ -1514,16 +1510,19 @@ __global__ __launch_bounds__(kThreads, 5) void k_march(CamDev c, const float* __
     march_tile<kAdj>(c, blockIdx.x, in, yout, xacc, smem, wsum);
 }
 
-// Persistent sweeps' cameras: forward, adjoint ray by ray, adjoint in bundles,
-// or adjoint cameras of both kinds.
-enum class Sweep { forward, rays, bundles, mixed };
+// Persistent sweeps' cameras: forward, adjoint ray by ray, adjoint in bundles with a
+// wave to a unit, with a workgroup to one, with either, or adjoints of any kind.
+enum class Sweep { forward, rays, waves, groups, bundles, mixed };
 
 // Persistent sweep over many (plan, camera, tile) items: each workgroup
 // takes the next item from a global counter until the list is exhausted
 // (every workgroup reaches the exit once the counter passes n_items).
-// Items are ordered by decreasing estimated cost.
+// Items are ordered by decreasing estimated cost.  Adjoints of one kind have a kernel of
+// that alone: beside another's code more of a bundle's registers lie in scratch memory
+// (waves 128 bytes a lane, groups 144, either 232, any kind 508; 48 frames of 4 cameras
+// by waves: adjoint sweep 120 ms with code for either, 111 with that for waves).
 template <Sweep kSweep>
-__global__ __launch_bounds__(kThreads, kSweep == Sweep::bundles || kSweep == Sweep::mixed ? 4 : 5) void k_batch(
+__global__ __launch_bounds__(kThreads, kSweep == Sweep::forward || kSweep == Sweep::rays ? 5 : 4) void k_batch(
     const BatchCam* __restrict__ cams, const uint32_t* __restrict__ items, uint32_t n_items,
     unsigned int* __restrict__ counter)
 {
@@ -1543,11 +1542,18 @@ __global__ __launch_bounds__(kThreads, kSweep == Sweep::bundles || kSweep == Swe
         if constexpr (kSweep == Sweep::forward) {
             march_tile<false>(bc.cam, tile, bc.x, bc.y, nullptr, smem, wsum);
         } else {
-            if (kSweep == Sweep::bundles || (kSweep == Sweep::mixed && bc.cam.bundle)) {
+            constexpr bool kMixed = kSweep == Sweep::mixed, kBoth = kMixed || kSweep == Sweep::bundles;
+            if (kSweep != Sweep::rays && (!kMixed || bc.cam.bundle)) {
+                const CamPtr c = (CamPtr)(uintptr_t)&bc.cam;
+                float4* const lds = reinterpret_cast<float4*>(smem);
                 const int t0 = tile * bc.item_tiles, t1 = min(t0 + bc.item_tiles, bc.cam.n_tiles);
-                for (int t = t0; t < t1; ++t)
-                    bundle_tile((CamPtr)(uintptr_t)&bc.cam, t, bc.y, bc.xacc, reinterpret_cast<float4*>(smem), wsum);
-            } else if constexpr (kSweep != Sweep::bundles) {
+                for (int t = t0; t < t1; ++t) {
+                    if (kSweep == Sweep::groups || (kBoth && fresh(c).ub_shared))
+                        bundle_tile<true>(c, t, bc.y, bc.xacc, lds, wsum);
+                    else if constexpr (kSweep != Sweep::groups)
+                        bundle_tile<false>(c, t, bc.y, bc.xacc, lds, wsum);
+                }
+            } else if constexpr (kSweep == Sweep::rays || kMixed) {
                 march_tile<true>(bc.cam, tile, bc.y, nullptr, bc.xacc, smem, wsum);
             }
         }
@@ -1729,12 +1735,16 @@ hipError_t launch_project(const CamDev& c, const float* x, float* y, hipStream_t
 namespace {
 typedef void (*BatchKernel)(const BatchCam*, const uint32_t*, uint32_t, unsigned int*);
 
-// kinds: bit 0 set when some camera's adjoint scatters ray by ray, bit 1 when
-// some camera's scatters in bundles
+// kinds: bits of the ways in which some camera's adjoint scatters: 0 ray by ray, 1 in
+// bundles with a wave to a unit, 2 with a workgroup
 BatchKernel batch_kernel(int dir, int kinds)
 {
     if (dir != LTM_ADJOINT) return k_batch<Sweep::forward>;
-    return kinds == 1 ? k_batch<Sweep::rays> : (kinds == 2 ? k_batch<Sweep::bundles> : k_batch<Sweep::mixed>);
+    return kinds == 1   ? k_batch<Sweep::rays>
+           : kinds == 2 ? k_batch<Sweep::waves>
+           : kinds == 4 ? k_batch<Sweep::groups>
+           : kinds == 6 ? k_batch<Sweep::bundles>
+                        : k_batch<Sweep::mixed>;
 }
 }  // namespace
 
