@@ -408,7 +408,10 @@ ltm_status ltm_autotune(ltm_plan* p, const float* x, const float* y, void* ws, u
             ltm_tiling cached{};
             double t_ms = 0.0;
             if (hit != cache.end() && parse_tiling(hit->second.tiling, cached)) {
-                if ((st = consider(cached, t_ms)) != LTM_OK) return st;
+                if (same_bundles(c, dir, cached, current) && check_tiling(p->grid, c.desc, cached) == LTM_OK)
+                    best = cached;   // the launch that was timed
+                else if ((st = consider(cached, t_ms)) != LTM_OK)
+                    return st;
             } else {
                 std::vector<std::pair<double, ltm_tiling>> timed;
                 for (const ltm_tiling& t : shape_candidates(p->grid, c, dir)) {
